@@ -151,6 +151,8 @@ struct hieravg {
   float* Gs = nullptr;     // [K1][P][Bp][Hp] hidden errors of the block's steps
   float* gram = nullptr;   // [KSG][K2][P][K1][K1][Bp][Bp] Gram blocks of the round
   int32_t* ylab = nullptr; // [T][P][B] labels of the drawn samples (delayed schedule)
+  uint32_t* mags = nullptr; // the magnitude tables of the delayed schedule (MagTables), one allocation
+  bool mags_valid = false;  // the last block's entries are those of the current W1 and buffers
   uint32_t* btab = nullptr; // [2][K2][P/S][Rp] row tables of the block update (BlkTables)
   float* part2 = nullptr;  // layer-2 split-K partials of the delayed schedule with more than 32 classes
   // Evaluation (allocated at the first hieravg_evaluate).
@@ -211,7 +213,7 @@ void release(hieravg* h) {
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   void* bufs[] = {h->W,  h->V,  h->Gr, h->Wm, h->X,  h->y,  h->idx, h->part, h->Z1, h->hyper, h->btab,
                   h->PL, h->G2, h->G1, h->ctr, h->Wc, h->Gs, h->gram, h->ylab, h->part2, h->flag, h->eval_iota,
-                  h->partv, h->Gu, h->Gt, h->Wc2, h->btab1, h->hgrad, h->Wg,
+                  h->partv, h->Gu, h->Gt, h->Wc2, h->btab1, h->hgrad, h->Wg, h->mags,
                   h->eval_part, h->eval_part2, h->eval_Z1, h->eval_loss, h->eval_hit, h->Xtest, h->ytest};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -357,7 +359,7 @@ int64_t plan(hieravg* h, int B) {
                 c.weight_decay == 0.0f;
   h->head_fused = mlp && c.classes <= kSmallC && head_fused_supported((int)h->Hp, (int)round_up(c.classes, 16));
   if (h->upd_mean) {
-    plan_split_blk(P / c.S, c.S * h->Bp, (int)n1, (int)h->INp, &h->KS_g, &h->cps_g);
+    plan_split(P / c.S, c.S * h->Bp, (int)n1, (int)h->INp, &h->KS_g, &h->cps_g);
     ks_max = std::max<int64_t>(ks_max, h->KS_g);
   }
   if (h->fused_mean) {
@@ -371,7 +373,7 @@ int64_t plan(hieravg* h, int B) {
   h->once_global = h->once_cond && h->once_alloc;
   h->once_block = h->once_global && h->upd_mean && c.S > 1;
   if (h->once_cond) {
-    plan_split_blk(1, P * h->Bp, (int)h->Hp, (int)h->INp, &h->KS_g0, &h->cps_g0);
+    plan_split(1, P * h->Bp, (int)h->Hp, (int)h->INp, &h->KS_g0, &h->cps_g0);
     ks_max = std::max<int64_t>(ks_max, h->KS_g0);
   }
   h->delayed = false;
@@ -391,15 +393,63 @@ int64_t plan(hieravg* h, int B) {
                    !(h->hb && c.K2 < 2);
   if (h->delayed) {
     // One GEMM per cluster and block: the K1*S minibatches against the copy.
-    plan_split_blk(P / c.S, c.K1 * c.S * h->Bp, (int)h->Hp, (int)h->INp, &h->KS_b, &h->cps_b);
+    plan_split(P / c.S, c.K1 * c.S * h->Bp, (int)h->Hp, (int)h->INp, &h->KS_b, &h->cps_b);
     ks_max = std::max<int64_t>(ks_max, (int64_t)h->KS_b * c.K1);
     // Heavy-ball with momentum: one more per learner, its K1 minibatches
     // against its own buffer.
     if (h->hb && c.momentum > 0.0f)
-      plan_split_blk(P, c.K1 * h->Bp, (int)h->Hp, (int)h->INp, &h->KSv, &h->cpsv);
+      plan_split(P, c.K1 * h->Bp, (int)h->Hp, (int)h->INp, &h->KSv, &h->cpsv);
   }
   h->ks_cur = h->KS1;
   return std::max<int64_t>(ks_max * P * h->Bp * n1, mlp ? (int64_t)h->KS2 * P * h->Bp * h->Cp : 0);
+}
+
+// The magnitude tables within h->mags.
+MagTables mag_tables(const hieravg* h) {
+  MagTables m;
+  m.K2 = h->cfg.K2;
+  m.G = h->cfg.P / h->cfg.S;
+  m.Hp = (int)h->Hp;
+  m.P = h->cfg.P;
+  const int64_t blk = (int64_t)m.K2 * m.G * m.Hp;
+  m.w0 = h->mags;
+  m.w = m.w0 + m.Hp;
+  m.g = m.w + blk;
+  if (h->hb && h->V) {
+    m.v0 = m.g + blk;
+    m.v = m.v0 + (int64_t)m.P * m.Hp;
+  }
+  return m;
+}
+
+// Power of two that brings the dataset's values into [2^14, 2^15): a class
+// mean and the noise are at most 6 standard deviations each.
+int x_exp(const hieravg* h) {
+  const float b = std::min(6.0f * (1.0f + std::fabs(h->cfg.noise_std)), 3.4e38f);
+  uint32_t bits;
+  std::memcpy(&bits, &b, sizeof(bits));
+  return 141 - (int)(bits >> 23);
+}
+
+// The rows of W1 (replica 0's) and of the buffers, measured into the tables
+// from which the next round starts: needed where something else than a
+// delayed round wrote them.
+hipError_t measure_mags(hieravg* h) {
+  const MagTables m = mag_tables(h);
+  const size_t row = sizeof(uint32_t) * m.Hp;
+  launch_row_maxima(h->stream, h->W + h->off_W1, 0, h->INp, h->INp, m.Hp, 1, m.w0);
+  for (int g = 0; g < m.G; ++g) {
+    const hipError_t e = hipMemcpyAsync(m.w + ((int64_t)(m.K2 - 1) * m.G + g) * m.Hp, m.w0, row,
+                                        hipMemcpyDeviceToDevice, h->stream);
+    if (e != hipSuccess) return e;
+  }
+  if (m.v0) {
+    launch_row_maxima(h->stream, h->V + h->off_W1, h->Dp, h->INp, h->INp, m.Hp, m.P, m.v0);
+    const hipError_t e = hipMemcpyAsync(m.v + (int64_t)(m.K2 - 1) * m.P * m.Hp, m.v0, row * m.P,
+                                        hipMemcpyDeviceToDevice, h->stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipGetLastError();
 }
 
 // The step size and the heavy-ball coefficient table, to the device.
@@ -536,6 +586,8 @@ int build(hieravg* h) {
       if ((rc = alloc_zero(h, (void**)&h->btab, 2 * sizeof(uint32_t) * (size_t)c.K2 * (P / c.S) * rp,
                            "block update row tables")))
         return rc;
+      const int64_t mag_n = h->Hp * (1 + 2 * (int64_t)c.K2 * (P / c.S) + (any_hb && h->V ? P * (1 + (int64_t)c.K2) : 0));
+      if ((rc = alloc_zero(h, (void**)&h->mags, sizeof(uint32_t) * mag_n, "magnitude tables"))) return rc;
       // more than 32 classes: the layer-2 partials of a step must not overwrite
       // the block forward's partials of the later steps
       if (h->C > kSmallC &&
@@ -652,7 +704,9 @@ bool launch_class(hieravg* h, int kc, int tt) {
   switch (kc) {
     case KC_DRAW: {
       BlkTables tb;
+      MagTables mg;
       if (h->in_delayed) {
+        mg = mag_tables(h);
         tb.Rp = (int)round_up((int64_t)c.K1 * S * B, 32);
         tb.gtab = h->btab;
         tb.xtab = h->btab + (int64_t)c.K2 * (P / S) * tb.Rp;
@@ -670,14 +724,14 @@ bool launch_class(hieravg* h, int kc, int tt) {
         }
       }
       launch_draw_indices(s, h->idx, h->ctr, (uint32_t*)(h->ctr + 1), P, B, h->T, (uint64_t)h->N,
-                          h->key_index, h->y, h->in_delayed ? h->ylab : nullptr, tb);
+                          h->key_index, h->y, h->in_delayed ? h->ylab : nullptr, tb, mg);
       return true;
     }
     case KC_FWD1: {
       if (tt == 0 && h->in_wg) {  // every learner's W1 is Wg: one GEMM over all P minibatches
         FwdArgs f{h->X, ix, h->INp, h->Wg, 0, h->INp, h->part, P, B, Bp, Hp, INp, h->KS_g0, h->cps_g0};
         f.SG = P;
-        launch_fwd_blk(s, f);
+        launch_fwd(s, f, A_GATHER);
         h->ks_cur = h->KS_g0;
         return true;
       }
@@ -754,7 +808,7 @@ bool launch_class(hieravg* h, int kc, int tt) {
       FwdArgs f{h->X, ix, h->INp, h->once_block ? h->Wc : W + h->off_W1, h->once_block ? w1 : (int64_t)S * h->Dp,
                 h->INp, h->part, P, B, Bp, Hp, INp, h->KS_g, h->cps_g};
       f.SG = S;
-      launch_fwd_blk(s, f);
+      launch_fwd(s, f, A_GATHER);
       h->ks_cur = h->KS_g;
       return true;
     }
@@ -779,7 +833,11 @@ bool launch_class(hieravg* h, int kc, int tt) {
       f.SG = c.K1 * S;
       f.vS = S;
       f.PT = c.K1 * P;
-      launch_fwd_blk(s, f);
+      const MagTables mg = mag_tables(h);
+      f.wmax = b == 0 ? mg.w0 : mg.w + (int64_t)(b - 1) * mg.G * Hp;
+      f.wmax_pitch = b == 0 ? 0 : Hp;
+      f.xexp = x_exp(h);
+      launch_fwd(s, f, A_GATHER);
       h->ks_cur = h->KS_b;
       return true;
     }
@@ -793,7 +851,11 @@ bool launch_class(hieravg* h, int kc, int tt) {
       f.SG = c.K1;
       f.vS = 1;
       f.PT = c.K1 * P;
-      launch_fwd_blk(s, f);
+      const MagTables mg = mag_tables(h);
+      f.wmax = b == 0 ? mg.v0 : mg.v + (int64_t)(b - 1) * P * Hp;
+      f.wmax_pitch = Hp;
+      f.xexp = x_exp(h);
+      launch_fwd(s, f, A_GATHER);
       return true;
     }
     case KC_SCALE_ERRORS:
@@ -816,6 +878,12 @@ bool launch_class(hieravg* h, int kc, int tt) {
       a.B2 = h->V + h->off_W1;
       a.b2_pitch = h->Dp;
       a.b2_rows = 1;
+      const MagTables mg = mag_tables(h);
+      a.gmax = mg.g + (int64_t)b * mg.G * Hp;
+      a.gm_div = S;
+      a.xexp = x_exp(h);
+      a.hb_g = hb_index(HB_T, 0);
+      a.wmax_out = mg.v + (int64_t)b * P * Hp;
       launch_block_update(s, a);
       return true;
     }
@@ -836,7 +904,13 @@ bool launch_class(hieravg* h, int kc, int tt) {
           a.b2_rows = S;
         }
       }
+      const MagTables mg = mag_tables(h);
+      a.gmax = mg.g + (int64_t)b * mg.G * Hp;
+      a.xexp = x_exp(h);
+      a.hb_g = hb_index(HB_U, 0);
+      a.wmax_out = mg.w + (int64_t)b * mg.G * Hp;
       if (b == c.K2 - 1 && h->global_last) {
+        a.gm_n = mg.G;
         // The last block: one update over all P learners from the mean of the
         // cluster copies (the global mean of Algorithm 1, which skips the
         // cluster mean before it), into replica 0's W1, and the global mean
@@ -978,6 +1052,8 @@ bool launch_class(hieravg* h, int kc, int tt) {
           a.vb2 = h->V + h->off_b2;
         }
       }
+      a.gmax = mag_tables(h).g + (int64_t)blk * (P / S) * Hp;
+      a.gS = S;
       launch_head_step(s, a, k);
       return true;
     }
@@ -998,7 +1074,8 @@ bool launch_class(hieravg* h, int kc, int tt) {
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->Gs + (int64_t)(tt % c.K1) * P * Bp * Hp, P, B,
                           Bp, C, Cp, Hp, W + h->off_b1, h->hyper, h->hb && h->V ? h->V + h->off_b1 : nullptr,
                           h->hb ? c.momentum : 0.0f, h->hb ? c.weight_decay : 0.0f,
-                          h->w2_fused ? W + h->off_b2 : nullptr);
+                          h->w2_fused ? W + h->off_b2 : nullptr,
+                          mag_tables(h).g + (int64_t)(tt / c.K1) * (P / S) * Hp, S);
       else if (h->w2_fused)
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->G1, P, B, Bp, C, Cp, Hp, nullptr, h->hyper,
                           nullptr, 0.0f, 0.0f, W + h->off_b2);
@@ -1481,6 +1558,11 @@ int hieravg_round(hieravg_t h) {
                                hipMemcpyDeviceToDevice, h->stream));
     h->rows_stale = false;
   }
+  if (h->in_delayed && !h->mags_valid) {
+    HAV_CHECK(measure_mags(h));
+    h->mags_valid = true;
+  }
+  if (!h->in_delayed) h->mags_valid = false;
   h->launch_failed = false;
   const char* refused = "a step launch of the round's plan was refused (internal error)";
   if (h->profiling) {
@@ -1718,6 +1800,7 @@ int hieravg_set_params(hieravg_t h, const float* src, size_t n_floats) {
       HAV_CHECK(hipMemcpy2DAsync(h->W + (int64_t)p * h->Dp + g.src_off, sizeof(float) * g.src_ld,
                                  src + (int64_t)p * h->D + g.dst_off, sizeof(float) * g.cols,
                                  sizeof(float) * g.cols, g.rows, hipMemcpyDefault, h->stream));
+  h->mags_valid = false;
   h->w1_shared = false;  // unless every row's W1 equals row 0's (a round-boundary checkpoint)
   h->rows_stale = false;
   h->w1_wg = false;
@@ -1788,6 +1871,7 @@ int hieravg_set_momentum(hieravg_t h, const float* src, size_t n_floats) {
     set_error("source holds fewer than P*D floats");
     return HIERAVG_ESIZE;
   }
+  h->mags_valid = false;
   HAV_CHECK(hipStreamSynchronize(h->stream));
   for (int p = 0; p < P; ++p)
     for (const Segment& g : segments(h))
@@ -1947,6 +2031,7 @@ int hieravg_time_kernel(hieravg_t h, int kernel_class, int reps, double* mean_ms
   // is launched once between the two events, so the host's per-launch cost
   // stays out of the timed interval.
   HAV_CHECK(hipStreamSynchronize(h->stream));
+  if (h->delayed && !h->mags_valid) HAV_CHECK(measure_mags(h));
   HAV_CHECK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
   bool ok = true;
   for (int i = 0; i < reps && ok; ++i) ok = launch_class(h, kernel_class, 0);

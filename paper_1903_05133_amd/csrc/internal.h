@@ -212,11 +212,29 @@ struct BlkTables {
   uint32_t* xtab1 = nullptr;
   int Rp1 = 0;
 };
+// Largest magnitudes of the delayed schedule's operands, as float bits: the
+// scales of their f16 parts (split.h).  w0: rows of W1 at the round start;
+// w: rows of the cluster copies written by each block's update ([K2][G][Hp],
+// the last block's global result in its first entry); g: hidden units of the
+// block's errors ([K2][G][Hp], by cluster); v0, v (with buffers): rows of the
+// learners' buffers, [P][Hp] and [K2][P][Hp].  A round starts by taking w0
+// and v0 from the last block's entries and clearing the rest; the kernels
+// that write an operand raise its entries.
+struct MagTables {
+  uint32_t *w0 = nullptr, *w = nullptr, *g = nullptr, *v0 = nullptr, *v = nullptr;
+  int K2 = 0, G = 0, Hp = 0, P = 0;
+};
+// out[r] = the largest magnitude of row r of W (ld floats apart, n a multiple
+// of 4), rows r < nrows of `mats` matrices w_pitch floats apart; out is
+// [mats][nrows].
+void launch_row_maxima(hipStream_t s, const float* W, int64_t w_pitch, int64_t ld, int64_t n, int nrows, int mats,
+                       uint32_t* out);
 // ylab (optional): the label of every drawn sample, same layout as idx.
+// mag.w0 (optional): also start the round's magnitude tables.
 // tables.gtab (optional): also write the block update's row tables.
 void launch_draw_indices(hipStream_t s, int32_t* idx, uint64_t* step_ctr, uint32_t* done_ctr, int P, int B,
                          int T, uint64_t N, uint64_t key, const int32_t* labels = nullptr, int32_t* ylab = nullptr,
-                         const BlkTables& tables = BlkTables());
+                         const BlkTables& tables = BlkTables(), const MagTables& mag = MagTables());
 
 // GEMMs (k_gemm.hip).
 struct FwdArgs {
@@ -231,26 +249,30 @@ struct FwdArgs {
   // Learners p = g*SG .. g*SG+SG-1 form row group g (SG*Mp rows of one GEMM)
   // and read weight copy g / wdiv (w_pitch 0: one copy for all).
   int SG = 1, wdiv = 1;
-  int mb_max = 8;  // largest row tile, in 16-row blocks (1, 2, 4 or 8)
   // vS > 0: the SG members of group g are (step k, learner g*vS + j) for
   // v = k*vS + j, whose sample indices sit at idx + (k*P + g*vS + j)*M and
   // whose outputs go to part[ks][k][P][Mp][N] (PT = steps * P members per
   // split).  idx then points at the first step's indices.
   int vS = 0, PT = 0;
+  // wmax set: the largest magnitude of each row of W (float bits; copy c's N
+  // values at + c*wmax_pitch, an upper bound does), and xexp the power of two
+  // that brings A's into [2^14, 2^15): the product of two f16 parts (split.h).
+  const uint32_t* wmax = nullptr;
+  int64_t wmax_pitch = 0;
+  int xexp = 0;
 };
 enum ASource { A_GATHER = 0, A_RELU = 1 };
 void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src);
-// Split count for a forward over P row groups of Mp rows each.
-void plan_split(int P, int Mp, int N, int K, int* KS, int* cps, int target_wg = 0, int mb_max = 8);
-// Large-tile forward (128 x 128 tiles, 1024 threads) for many rows per weight
-// copy, and its split count.
-void launch_fwd_blk(hipStream_t s, const FwdArgs& a);
-void plan_split_blk(int groups, int rows, int N, int K, int* KS, int* cps);
-// Workgroup target of the block-wide forward from the cluster copies.
-#ifndef HAV_FWD_BLOCK_TARGET
-#define HAV_FWD_BLOCK_TARGET 256
-#endif
-int fwd_tiles(int P, int Mp, int N);
+// Split count of a forward over `groups` row groups of GM rows each, no empty
+// split.
+void plan_split(int groups, int GM, int N, int K, int* KS, int* cps);
+// Outputs of 64 columns and more run as split products in 128- or 256-column
+// tiles (k_split.hip), narrower ones (the logits of few classes) as 16-column
+// float32 MFMA blocks (k_gemm.hip): there a wide tile is mostly padding (4 x 16
+// rows of 16 columns over 3072 features take 5.6 us).
+inline bool fwd_split_takes(int N) { return N >= 64; }
+void launch_fwd_nt(hipStream_t s, const FwdArgs& a, ASource src);
+void plan_split_nt(int groups, int GM, int N, int K, int* KS, int* cps);
 
 struct UpdArgs {
   const float* G;       // [P][Mp][ldg] error rows (row s = sample, column m = output unit)
@@ -314,6 +336,14 @@ struct BlkArgs {
   const float* B2 = nullptr;
   int64_t b2_pitch = 0;
   int b2_rows = 0;
+  // Magnitudes: the error rows' largest per unit, as float bits [..][Mrows]:
+  // group g takes the larger of entries (g/gm_div)*gm_n .. +gm_n-1 (before
+  // the coefficients hb[hb_g + k] that scaled errors carry); xexp as in
+  // FwdArgs.  wmax_out (optional, [P/SG][Mrows]): raised to the largest
+  // magnitude of each result row.
+  const uint32_t* gmax = nullptr;
+  int gm_div = 1, gm_n = 1, xexp = 0, hb_g = 0;
+  uint32_t* wmax_out = nullptr;
 };
 // Largest contraction (K1 * SG * B rows) of a block update.
 constexpr int kBlkMaxRows = 16384;
@@ -378,9 +408,11 @@ void launch_softmax_grad(hipStream_t s, const float* part, int KS, const float* 
 // b2 (M <= 32, plain SGD; lr required): also the second layer's step,
 // W2 -= lr * G2^T relu(Z1) and b2 -= lr * column sums of G2, in the same pass
 // over W2 (no update GEMM for this layer).
+// gmax (optional, [P/gS][Hp], M <= 32): raised to the largest |G1| of each unit
+// over a cluster's samples.
 void launch_bwd_hidden(hipStream_t s, const float* G2, float* W2, int64_t w_pitch, const float* Z1, float* G1, int P,
                        int M, int Mp, int C, int Cp, int Hp, float* b1 = nullptr, const float* lr = nullptr,
-                       float* vb1 = nullptr, float mu = 0.0f, float wd = 0.0f, float* b2 = nullptr);
+                       float* vb1 = nullptr, float mu = 0.0f, float wd = 0.0f, float* b2 = nullptr, uint32_t* gmax = nullptr, int gS = 1);
 // Whether launch_bwd_hidden takes the second layer's step for M samples.
 bool bwd_hidden_update_supported(int M, int Cp);
 // Heavy-ball delayed updates, after a block's last step: Gu[k] = u_{K1-1-k}
@@ -484,6 +516,8 @@ struct HeadStepArgs {
   float* vb1 = nullptr;
   float* vb2 = nullptr;
   float mu = 0.0f, wd = 0.0f;
+  uint32_t* gmax = nullptr;  // [P/gS][Hp] of the block: raised to each unit's largest error
+  int gS = 1;
 };
 // One launch for step k.
 void launch_head_step(hipStream_t s, const HeadStepArgs& a, int k);

@@ -69,7 +69,27 @@ __global__ __launch_bounds__(256) void k_gen_grads(float* __restrict__ G, int64_
 __global__ __launch_bounds__(256) void k_draw_indices(int32_t* __restrict__ idx, uint64_t* step_ctr,
                                                       uint32_t* done_ctr, int P, int B, int T, uint64_t N,
                                                       uint64_t key, const int32_t* __restrict__ labels,
-                                                      int32_t* __restrict__ ylab, BlkTables tb) {
+                                                      int32_t* __restrict__ ylab, BlkTables tb,
+                                                      MagTables mg) {
+  if (mg.w0) {
+    const int64_t step = (int64_t)gridDim.x * 256, me = blockIdx.x * 256ll + threadIdx.x;
+    auto start = [&](uint32_t* dst, uint32_t* tab, int n, int64_t per, bool over) {
+      // dst = the last of the n entries of `per` values (over: the largest of
+      // its G rows), which is then cleared with the others
+      const int64_t len = over ? mg.Hp : per;
+      for (int64_t i = me; i < len; i += step) {
+        uint32_t m = 0;
+        for (int64_t o = i; o < per; o += len) {
+          m = max(m, tab[(n - 1) * per + o]);
+          for (int b = 0; b < n; ++b) tab[b * per + o] = 0;
+        }
+        dst[i] = m;
+      }
+    };
+    start(mg.w0, mg.w, mg.K2, (int64_t)mg.G * mg.Hp, true);
+    if (mg.v0) start(mg.v0, mg.v, mg.K2, (int64_t)mg.P * mg.Hp, false);
+    for (int64_t i = me; i < (int64_t)mg.K2 * mg.G * mg.Hp; i += step) mg.g[i] = 0;
+  }
   const uint64_t t0 = *step_ctr;
   const int64_t total = (int64_t)T * P * B;
   for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
@@ -148,9 +168,33 @@ void launch_gen_grads(hipStream_t s, float* G, int64_t D, int64_t Dp, int P, int
 
 void launch_draw_indices(hipStream_t s, int32_t* idx, uint64_t* step_ctr, uint32_t* done_ctr, int P, int B,
                          int T, uint64_t N, uint64_t key, const int32_t* labels, int32_t* ylab,
-                         const BlkTables& tables) {
+                         const BlkTables& tables, const MagTables& mag) {
   launch(k_draw_indices, grid_for((int64_t)T * P * B, 1024), 256, 0, s, idx, step_ctr, done_ctr, P, B, T, N, key,
-         labels, ylab, tables);
+         labels, ylab, tables, mag);
+}
+
+// One workgroup per row: the largest magnitude, as float bits (NaN and
+// infinity above all).
+__global__ __launch_bounds__(256) void k_row_maxima(const float* __restrict__ W, int64_t w_pitch, int64_t ld, int64_t n,
+                                                    int nrows, uint32_t* __restrict__ out) {
+  __shared__ uint32_t part[256];
+  const uint4* row = (const uint4*)(W + (int64_t)(blockIdx.x / nrows) * w_pitch + (int64_t)(blockIdx.x % nrows) * ld);
+  uint32_t m = 0;
+  for (int64_t i = threadIdx.x; i < n / 4; i += 256) {
+    const uint4 v = row[i];
+    m = max(m, max(max(v.x & 0x7fffffffu, v.y & 0x7fffffffu), max(v.z & 0x7fffffffu, v.w & 0x7fffffffu)));
+  }
+  part[threadIdx.x] = m;
+  for (int o = 128; o > 0; o >>= 1) {
+    __syncthreads();
+    if ((int)threadIdx.x < o) part[threadIdx.x] = max(part[threadIdx.x], part[threadIdx.x + o]);
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = part[0];
+}
+
+void launch_row_maxima(hipStream_t s, const float* W, int64_t w_pitch, int64_t ld, int64_t n, int nrows, int mats,
+                       uint32_t* out) {
+  launch(k_row_maxima, (unsigned)((int64_t)nrows * mats), 256, 0, s, W, w_pitch, ld, n, nrows, out);
 }
 
 }  // namespace hav

@@ -3,6 +3,7 @@
 // w <- w - lr * g), batched over the P learners and run on fp32 MFMA.
 //
 // k_fwd_nt:    part[ks][p][m][n] = sum_{k in split ks} A_p[m][k] * W_p[n][k]
+//              for narrow outputs (N < 64; wider ones run in k_split.hip)
 //              (A = gathered minibatch rows of X, or ReLU of the hidden
 //              pre-activations; W = a weight block, K-contiguous), split
 //              over K so the launch fills the GPU.  The consumer adds the
@@ -30,11 +31,11 @@ constexpr int kLdsStride = 68;  // LDS row stride in floats (64 + 4: conflict-fr
 #endif
 constexpr int kFwdTargetWG = HAV_FWD_TARGET_WG;  // workgroups a forward launch aims for
 
-__device__ inline f32x4 relu4(f32x4 v) {
-  v.x = fmaxf(v.x, 0.0f);
-  v.y = fmaxf(v.y, 0.0f);
-  v.z = fmaxf(v.z, 0.0f);
-  v.w = fmaxf(v.w, 0.0f);
+__device__ inline f32x4 relu4(f32x4 v) {  // NaN stays NaN
+  v.x = v.x < 0.0f ? 0.0f : v.x;
+  v.y = v.y < 0.0f ? 0.0f : v.y;
+  v.z = v.z < 0.0f ? 0.0f : v.z;
+  v.w = v.w < 0.0f ? 0.0f : v.w;
   return v;
 }
 
@@ -189,35 +190,26 @@ __global__ __launch_bounds__(256) void k_fwd_nt(FwdArgs a, int ntiles, int mtile
     }
 }
 
-static int pick_mb(int Mp, int mb_max = 8) {
-  const int mb = Mp >= 128 ? 8 : Mp >= 64 ? 4 : Mp >= 32 ? 2 : 1;
-  return mb < mb_max ? mb : mb_max;
-}
+static int pick_mb(int GM) { return GM >= 128 ? 8 : GM >= 64 ? 4 : GM >= 32 ? 2 : 1; }
 
-void plan_split(int P, int Mp, int N, int K, int* KS, int* cps, int target_wg, int mb_max) {
-  // Enough K splits that the launch has about target_wg workgroups (the GEMMs
-  // have few output tiles per learner: M is the minibatch), and no empty split.
-  if (target_wg <= 0) target_wg = kFwdTargetWG;
-  const int MB = pick_mb(Mp, mb_max);
-  const int mtiles = (Mp + MB * 16 - 1) / (MB * 16);
+void plan_split_nt(int groups, int GM, int N, int K, int* KS, int* cps) {
+  // Enough K splits that the launch has about kFwdTargetWG workgroups (the
+  // GEMMs have few output tiles per learner: M is the minibatch), and no empty
+  // split.
+  const int MB = pick_mb(GM);
+  const int mtiles = (GM + MB * 16 - 1) / (MB * 16);
   const int nch = K / kKC;
-  const int64_t tiles = (int64_t)P * mtiles * ((N + 127) / 128);
-  int ks = (int)std::max<int64_t>(1, (target_wg + tiles - 1) / tiles);
+  const int64_t tiles = (int64_t)groups * mtiles * ((N + 127) / 128);
+  int ks = (int)std::max<int64_t>(1, (kFwdTargetWG + tiles - 1) / tiles);
   ks = std::min(ks, nch);
   const int c = (nch + ks - 1) / ks;
   *KS = (nch + c - 1) / c;
   *cps = c;
 }
 
-int fwd_tiles(int P, int Mp, int N) {
-  const int MB = pick_mb(Mp);
-  const int mtiles = (Mp + MB * 16 - 1) / (MB * 16);
-  return P * mtiles * ((N + 127) / 128);
-}
-
-void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
+void launch_fwd_nt(hipStream_t s, const FwdArgs& a, ASource src) {
   const int GM = a.SG * a.Mp;
-  const int MB = pick_mb(GM, a.mb_max);
+  const int MB = pick_mb(GM);
   const int mtiles = (GM + MB * 16 - 1) / (MB * 16);
   const int ntiles = (a.N + 127) / 128;
   const int groups = a.vS > 0 ? a.P / a.vS : a.P / a.SG;

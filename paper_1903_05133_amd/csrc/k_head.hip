@@ -235,7 +235,8 @@ __global__ __launch_bounds__(256) void k_bwd_hidden_mfma(const float* __restrict
                                                          float* __restrict__ G1, int M, int Mp, int Cp, int Hp,
                                                          int htiles, int mtiles, float* __restrict__ b1,
                                                          const float* __restrict__ lr_ptr, float* __restrict__ vb1,
-                                                         float mu, float wd, float* __restrict__ b2) {
+                                                         float mu, float wd, float* __restrict__ b2,
+                                                         uint32_t* __restrict__ gmax, int gS) {
   __shared__ __attribute__((aligned(16))) float lds[kBhLds];
   __shared__ float a1s[UPD ? kBhM : 1][kBhN + 1];  // relu(Z1) of the tile (UPD)
   // buffer b: G2 chunk [class][sample] at gsb(b), W2 chunk [class][unit] at wsb(b)
@@ -388,6 +389,7 @@ __global__ __launch_bounds__(256) void k_bwd_hidden_mfma(const float* __restrict
       zv[r] = Z1[((int64_t)p * Mp + min(m, M - 1)) * Hp + h];
     }
     float db = 0.0f;
+    uint32_t mag = 0;  // bits of the largest magnitude (NaN and infinity above all)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 8 * (r >> 2) + 4 * lhi + (r & 3), m = m0 + row;
@@ -396,7 +398,12 @@ __global__ __launch_bounds__(256) void k_bwd_hidden_mfma(const float* __restrict
         const float g1 = zv[r] > 0.0f ? g : 0.0f;
         G1[((int64_t)p * Mp + m) * Hp + h] = g1;
         db += g1;
+        mag = max(mag, __builtin_bit_cast(uint32_t, g1) & 0x7fffffffu);
       }
+    }
+    if (gmax) {
+      mag = max(mag, (uint32_t)__shfl_xor((int)mag, 32, 64));
+      if (lhi == 0) atomicMax(gmax + (int64_t)(p / gS) * Hp + h, mag);
     }
     if (b1) {  // rows 0-3, 8-11, ... of lanes 0-31, then the other rows of lanes 32-63
       const float other = __shfl_xor(db, 32, 64);
@@ -1058,7 +1065,7 @@ __global__ __launch_bounds__(256) void k_head_step(HeadStepArgs a, int htiles, i
   // wait between them: the addresses are clamped into the buffers instead of
   // branched around per thread, and values are masked where they are used.
   // Step k's partials, first kPv splits (the rest, if any, are added in (B)).
-  constexpr int kPv = 4;
+  constexpr int kPv = 8;
   const int kc = k < a.K1 ? k : 0;  // earlier steps whose correction (B) applies
   f32x4 pv[kPv];
   if (k < a.K1) {
@@ -1238,6 +1245,14 @@ __global__ __launch_bounds__(256) void k_head_step(HeadStepArgs a, int htiles, i
       for (int e = 0; e < 8; ++e) {
         const int mm = 16 * (e >> 2) + 4 * lq + (e & 3);
         if (mm < M) g1out[(int64_t)mm * Hp] = g1[e];
+      }
+      if (a.gmax) {  // the unit's largest error (bits; NaN and infinity above all)
+        uint32_t mag = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mag = max(mag, __builtin_bit_cast(uint32_t, g1[e]) & 0x7fffffffu);
+        mag = max(mag, (uint32_t)__shfl_xor((int)mag, 16));
+        mag = max(mag, (uint32_t)__shfl_xor((int)mag, 32));
+        if (lq == 0) atomicMax(a.gmax + (int64_t)(p / a.gS) * Hp + ht * kHU + uu, mag);
       }
       db1 += __shfl_xor(db1, 16);
       db1 += __shfl_xor(db1, 32);
@@ -1525,7 +1540,7 @@ void launch_scale_errors(hipStream_t s, const float* Gs, float* Gu, float* Gt, c
 
 void launch_bwd_hidden(hipStream_t s, const float* G2, float* W2, int64_t w_pitch, const float* Z1, float* G1, int P,
                        int M, int Mp, int C, int Cp, int Hp, float* b1, const float* lr, float* vb1, float mu, float wd,
-                       float* b2) {
+                       float* b2, uint32_t* gmax, int gS) {
   if (b1 && M > kBhM) {  // the b1 step needs every sample in one workgroup
     const int htiles = (Hp + 63) / 64;
     launch(k_bwd_hidden, P * htiles, 256, 0, s, G2, W2, w_pitch, Z1, G1, M, Mp, C, Cp, Hp, htiles, b1, lr);
@@ -1535,10 +1550,10 @@ void launch_bwd_hidden(hipStream_t s, const float* G2, float* W2, int64_t w_pitc
   const unsigned grid = (unsigned)((int64_t)P * mtiles * htiles);
   if (b2)
     launch(k_bwd_hidden_mfma<true>, grid, 256, 0, s, G2, W2, w_pitch, Z1, G1, M, Mp, Cp, Hp, htiles, mtiles, b1, lr, vb1,
-           mu, wd, b2);
+           mu, wd, b2, gmax, gS);
   else
     launch(k_bwd_hidden_mfma<false>, grid, 256, 0, s, G2, W2, w_pitch, Z1, G1, M, Mp, Cp, Hp, htiles, mtiles, b1, lr,
-           vb1, mu, wd, (float*)nullptr);
+           vb1, mu, wd, (float*)nullptr, gmax, gS);
 }
 
 bool bwd_hidden_update_supported(int M, int Cp) { return M <= kBhM && Cp <= kBhMaxC; }

@@ -1,0 +1,94 @@
+"""The wide contractions as split float32 products (csrc/split.h,
+csrc/k_split.hip): every tile of the forward and of the block update at its
+edges, and operands of very different magnitudes, against the CPU oracle.
+
+Tolerance: the 1e-4 gate of the parity tests for whole parameter blocks.  For
+the magnitudes test the same 1e-4 holds for every hidden unit by itself:
+each row of W1 has its own scale, so a unit's relative error (float32
+rounding of sums of at most 200 terms, about 1e-6) does not depend on the
+other units' magnitudes.
+"""
+
+import numpy as np
+import pytest
+
+import cases
+from oracle import method as M
+from test_gpu_parity import TOL, _check, _oracle, _run_gpu
+
+pytestmark = pytest.mark.gpu
+
+# name -> (case, mode, tile it is there for)
+TILES = {
+    # forward tiles by rows per group: 32 (one padded 16-row minibatch), 64
+    # (33 samples, 48 rows), 128 (65 samples, 80 rows; 150: two row tiles)
+    "rows_16": (cases.case("mlp", 3, 1, 2, 1, B=16, IN=65, H=65, C=40, N=90, lr=0.1, seed=201), "eager"),
+    "rows_48": (cases.case("mlp", 4, 2, 2, 1, B=33, IN=190, H=130, C=70, N=90, lr=0.05, seed=202), "eager"),
+    "rows_80": (cases.case("mlp", 2, 2, 2, 1, B=65, IN=320, H=100, C=130, N=90, lr=0.05, seed=203), "eager"),
+    "rows_160": (cases.case("mlp", 2, 1, 1, 2, B=150, IN=129, H=192, C=33, N=90, lr=0.05, seed=204), "eager"),
+    # 128 x 256 tiles, full and ragged in rows, units and features; the block
+    # update in 64 x 64 tiles
+    "delayed_full": (cases.case("mlp", 16, 4, 4, 2, B=32, IN=512, H=256, C=7, N=300, sigma=0.5, lr=0.05, seed=205),
+                     "delayed"),
+    "delayed_ragged": (cases.case("mlp", 12, 3, 3, 2, B=27, IN=333, H=300, C=37, N=300, sigma=0.5, lr=0.05, seed=206),
+                       "delayed"),
+    # 256 x 256 forward tiles (16 groups of 256 rows, 1024 units, 4 splits of
+    # 1024 features); the block update in 128 x 256 tiles
+    "delayed_256": (cases.case("mlp", 32, 2, 8, 1, B=16, IN=4096, H=1024, C=5, N=300, sigma=0.5, lr=0.05, seed=207),
+                    "delayed"),
+    # 128 x 128 block-update tiles, ragged (320 units, 3008 features)
+    "delayed_update_128": (cases.case("mlp", 16, 4, 2, 2, B=9, IN=3001, H=310, C=5, N=300, sigma=0.5, lr=0.05, seed=208),
+                           "delayed"),
+    # one step per block, one sample: the shortest contractions
+    "delayed_one_sample": (cases.case("mlp", 2, 1, 1, 2, B=1, IN=64, H=64, C=3, N=30, lr=0.1, seed=209), "delayed"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(TILES))
+def test_tiles_match_oracle(name, gpu_lib):
+    c, mode = TILES[name]
+    rounds = 1 if name == "delayed_256" else 2
+    got, idx, _ = _run_gpu(c, rounds, mode)
+    _check(c, got, idx, *_oracle(c, rounds), mode=mode)
+
+
+@pytest.mark.parametrize("mode", ["delayed", "eager"])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_units_of_any_magnitude(mode, momentum, gpu_lib):
+    """Rows of W1 scaled by 10^-12 .. 10^12 (their W2 columns by the inverse,
+    so the logits stay ordinary): every unit keeps its own relative accuracy."""
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("mlp", 4, 2, 2, 2, B=16, IN=200, H=96, C=5, N=300, sigma=0.5, lr=1e-3, momentum=momentum, seed=211)
+    prob = cases.oracle_problem(c)
+    scale = 10.0 ** np.linspace(-12, 12, prob.H)
+    st = M.create(prob)
+    for p in range(prob.P):
+        b = M.unpack(prob, st.W[p])
+        b["W1"] *= scale[:, None]
+        b["W2"] /= scale[None, :]
+    st.W[:] = st.W.astype(np.float32).astype(np.float64)
+    print(f"[gpu case] {mode} {c}", flush=True)
+    with HierAvg(config=cases.native_config(c, mode)) as h:
+        h.set_params(st.W.astype(np.float32))
+        h.round()
+        got = h.params()
+    M.hieravg_round(prob, st)
+    for p in range(prob.P):
+        g, w = M.unpack(prob, got[p].astype(np.float64)), M.unpack(prob, st.W[p])
+        err = np.abs(g["W1"] - w["W1"]).max(axis=1) / np.abs(w["W1"]).max(axis=1)
+        assert err.max() <= TOL, (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_non_finite_weights_stay_visible(value, gpu_lib):
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("mlp", 4, 2, 2, 2, B=16, IN=200, H=96, C=5, N=300, sigma=0.5, lr=1e-3, seed=212)
+    print(f"[gpu case] {value} {c}", flush=True)
+    with HierAvg(config=cases.native_config(c, "delayed")) as h:
+        w = h.params()
+        w[:, 200 * 7 + 3] = value
+        h.set_params(w)
+        assert not h.finite()
+        assert not np.isfinite(h.evaluate(0, 0, 64)[0])
+        h.round()
+        assert not h.finite()
