@@ -1202,6 +1202,72 @@ std::vector<Segment> segments(const hieravg* h) {
           {1, h->C, h->C, h->off_b2, o3}};
 }
 
+// Makes `dev` current for a scope and restores the caller's device.
+struct DeviceGuard {
+  int prev = -1;
+  int enter(int dev) {
+    if (hipGetDevice(&prev) != hipSuccess) {
+      prev = -1;
+      set_error("hipGetDevice failed");
+      return HIERAVG_EHIP;
+    }
+    if (prev != dev && hipSetDevice(dev) != hipSuccess) {
+      set_error("hipSetDevice to the handle's device failed");
+      return HIERAVG_EHIP;
+    }
+    return HIERAVG_OK;
+  }
+  ~DeviceGuard() {
+    if (prev >= 0) (void)hipSetDevice(prev);
+  }
+};
+
+// Whether `ptr` is memory of device `dev` that a kernel on it may write.
+bool on_device(const void* ptr, int dev) {
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, ptr) != hipSuccess) {
+    (void)hipGetLastError();  // ordinary host memory
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
+// The learners' rows of `rows` (replicas or buffers; `common`, if set: the
+// first block of every learner) as a dense [P][D] array at dst, in host or
+// device memory.  Synchronous.
+int read_rows(hieravg* h, const float* rows, const float* common, float* dst) {
+  const int P = h->cfg.P;
+  const std::vector<Segment> segs = segments(h);
+  if (((uintptr_t)dst % sizeof(float)) == 0 && on_device(dst, h->device)) {
+    DeviceGuard dg;
+    int rc;
+    if ((rc = dg.enter(h->device)) != HIERAVG_OK) return rc;
+    PackArgs a;
+    a.nseg = (int)segs.size();
+    a.P = P;
+    a.D = h->D;
+    a.dst = dst;
+    for (size_t i = 0; i < segs.size(); ++i) {
+      const Segment& g = segs[i];
+      const bool one = i == 0 && common;
+      a.seg[i] = {(one ? common : rows) + g.src_off, one ? 0 : h->Dp, g.rows, g.cols, g.src_ld, g.dst_off, 0};
+    }
+    launch_pack(h->stream, a);
+    HAV_CHECK(hipGetLastError());
+  } else {
+    for (int p = 0; p < P; ++p)
+      for (size_t i = 0; i < segs.size(); ++i) {
+        const Segment& g = segs[i];
+        const float* src = i == 0 && common ? common : rows + (int64_t)p * h->Dp;
+        HAV_CHECK(hipMemcpy2DAsync(dst + (int64_t)p * h->D + g.dst_off, sizeof(float) * g.cols, src + g.src_off,
+                                   sizeof(float) * g.src_ld, sizeof(float) * g.cols, g.rows, hipMemcpyDefault,
+                                   h->stream));
+      }
+  }
+  HAV_CHECK(hipStreamSynchronize(h->stream));
+  return HIERAVG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1477,26 +1543,6 @@ int scratch_on_device(int dev, float** out) {
   return HIERAVG_OK;
 }
 
-// Makes `dev` current for a scope and restores the caller's device.
-struct DeviceGuard {
-  int prev = -1;
-  int enter(int dev) {
-    if (hipGetDevice(&prev) != hipSuccess) {
-      prev = -1;
-      set_error("hipGetDevice failed");
-      return HIERAVG_EHIP;
-    }
-    if (prev != dev && hipSetDevice(dev) != hipSuccess) {
-      set_error("hipSetDevice to the handle's device failed");
-      return HIERAVG_EHIP;
-    }
-    return HIERAVG_OK;
-  }
-  ~DeviceGuard() {
-    if (prev >= 0) (void)hipSetDevice(prev);
-  }
-};
-
 // Largest chunk (rows, a multiple of 16 up to kEvalMaxChunk) whose buffers fit
 // in the scratch array with one split each, and the partial capacities.
 int eval_scratch_plan(const hieravg* h, int* rows, int64_t* part_cap, int64_t* part2_cap) {
@@ -1767,21 +1813,11 @@ int hieravg_params(hieravg_t h, float* dst, size_t n_floats) {
               std::to_string((int64_t)P * h->D));
     return HIERAVG_ESIZE;
   }
-  HAV_CHECK(hipStreamSynchronize(h->stream));
-  const std::vector<Segment> segs = segments(h);
-  for (int p = 0; p < P; ++p)
-    for (size_t i = 0; i < segs.size(); ++i) {
-      const Segment& g = segs[i];
-      // After delayed updates only replica 0 holds the (common) W1; after an
-      // averaging-kind round Wm holds every learner's parameters.
-      const float* src = h->W + (int64_t)p * h->Dp;
-      if (i == 0 && h->rows_stale) src = h->cfg.kind == HIERAVG_KIND_AVERAGING ? h->Wm : h->w1_wg ? h->Wg : h->W;
-      HAV_CHECK(hipMemcpy2DAsync(dst + (int64_t)p * h->D + g.dst_off, sizeof(float) * g.cols, src + g.src_off,
-                                 sizeof(float) * g.src_ld, sizeof(float) * g.cols, g.rows, hipMemcpyDefault,
-                                 h->stream));
-    }
-  HAV_CHECK(hipStreamSynchronize(h->stream));
-  return HIERAVG_OK;
+  // After delayed updates only replica 0 holds the (common) W1; after an
+  // averaging-kind round Wm holds every learner's parameters.
+  const float* common =
+      !h->rows_stale ? nullptr : h->cfg.kind == HIERAVG_KIND_AVERAGING ? h->Wm : h->w1_wg ? h->Wg : h->W;
+  return read_rows(h, h->W, common, dst);
 }
 
 int hieravg_set_params(hieravg_t h, const float* src, size_t n_floats) {
@@ -1847,14 +1883,7 @@ int hieravg_momentum(hieravg_t h, float* dst, size_t n_floats) {
     set_error("destination holds fewer than P*D floats");
     return HIERAVG_ESIZE;
   }
-  HAV_CHECK(hipStreamSynchronize(h->stream));
-  for (int p = 0; p < P; ++p)
-    for (const Segment& g : segments(h))
-      HAV_CHECK(hipMemcpy2DAsync(dst + (int64_t)p * h->D + g.dst_off, sizeof(float) * g.cols,
-                                 h->V + (int64_t)p * h->Dp + g.src_off, sizeof(float) * g.src_ld,
-                                 sizeof(float) * g.cols, g.rows, hipMemcpyDefault, h->stream));
-  HAV_CHECK(hipStreamSynchronize(h->stream));
-  return HIERAVG_OK;
+  return read_rows(h, h->V, nullptr, dst);
 }
 
 int hieravg_set_momentum(hieravg_t h, const float* src, size_t n_floats) {

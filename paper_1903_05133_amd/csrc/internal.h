@@ -551,4 +551,21 @@ void launch_momentum_step(hipStream_t s, float* W, float* V, const float* Gr, in
                           bool average, const float* lr, float mu, float wd, const float* shared_in = nullptr,
                           float* mean_out = nullptr);
 
+// The replica rows of P learners to a dense [P][D] array in device memory:
+// per parameter block, `rows` rows of `cols` floats, ld floats apart at
+// src + p*pitch (pitch 0: one copy for every learner), to offset `off` of
+// each dense row.
+struct PackSeg {
+  const float* src = nullptr;
+  int64_t pitch = 0, rows = 0, cols = 0, ld = 0, off = 0;
+  int64_t blocks = 0;  // set by the launcher
+};
+struct PackArgs {
+  PackSeg seg[4];
+  int nseg = 0, P = 0;
+  int64_t D = 0;
+  float* dst = nullptr;
+};
+void launch_pack(hipStream_t s, PackArgs a);
+
 }  // namespace hav

@@ -292,4 +292,56 @@ void launch_momentum_step(hipStream_t s, float* W, float* V, const float* Gr, in
          (const f32x4*)(shared_in ? shared_in : W), shared_in ? 0 : n4, (f32x4*)io.mean_out);
 }
 
+// Replica rows to a dense [P][D] device array (PackArgs).  A workgroup copies
+// kPackU * 256 pieces of V floats of one parameter-block row, for one learner
+// or, of a block that the learners share, for up to kPackP learners from one
+// read.  Bound by HBM writes; V is the widest piece that every row start of the
+// dense array is aligned to (D, the block offsets and widths and the
+// destination).  16 replicas of 155M floats: 5.0 ms as one copy per learner
+// and block, 1.9 ms here (9.9 GB written at 5.2 TB/s).
+constexpr int kPackU = 8, kPackP = 16;
+template <int V>
+__global__ __launch_bounds__(256) void k_pack(PackArgs a) {
+  typedef float vec __attribute__((ext_vector_type(V)));
+  int64_t b = blockIdx.x;
+  int s = 0;
+  while (b >= a.seg[s].blocks) b -= a.seg[s++].blocks;
+  const PackSeg g = a.seg[s];
+  const int64_t cpr = (g.cols / V + 256 * kPackU - 1) / (256 * kPackU);  // workgroups per row
+  const int64_t pg = b / (g.rows * cpr), rc = b - pg * (g.rows * cpr);
+  const int64_t row = rc / cpr, c0 = (rc - row * cpr) * (256 * kPackU) + threadIdx.x;
+  const int np = g.pitch ? 1 : kPackP;
+  const int p0 = (int)pg * np, p1 = min(p0 + np, a.P);
+  const vec* src = (const vec*)(g.src + (int64_t)p0 * g.pitch + row * g.ld);
+  const int64_t n = g.cols / V;
+  vec v[kPackU];
+#pragma unroll
+  for (int u = 0; u < kPackU; ++u) v[u] = src[min(c0 + 256 * u, n - 1)];
+  for (int p = p0; p < p1; ++p) {
+    vec* dst = (vec*)(a.dst + (int64_t)p * a.D + g.off + row * g.cols);
+#pragma unroll
+    for (int u = 0; u < kPackU; ++u)
+      if (c0 + 256 * u < n) __builtin_nontemporal_store(v[u], dst + c0 + 256 * u);
+  }
+}
+
+void launch_pack(hipStream_t s, PackArgs a) {
+  int64_t unit = a.D | (int64_t)((uintptr_t)a.dst / sizeof(float));
+  for (int i = 0; i < a.nseg; ++i) unit |= a.seg[i].cols | a.seg[i].off;
+  const int V = unit % 4 == 0 ? 4 : unit % 2 == 0 ? 2 : 1;
+  int64_t blocks = 0;
+  for (int i = 0; i < a.nseg; ++i) {
+    PackSeg& g = a.seg[i];
+    const int64_t groups = g.pitch ? a.P : (a.P + kPackP - 1) / kPackP;
+    g.blocks = groups * g.rows * ((g.cols / V + 256 * kPackU - 1) / (256 * kPackU));
+    blocks += g.blocks;
+  }
+  if (V == 4)
+    launch(k_pack<4>, (unsigned)blocks, 256, 0, s, a);
+  else if (V == 2)
+    launch(k_pack<2>, (unsigned)blocks, 256, 0, s, a);
+  else
+    launch(k_pack<1>, (unsigned)blocks, 256, 0, s, a);
+}
+
 }  // namespace hav

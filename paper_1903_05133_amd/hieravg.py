@@ -76,6 +76,9 @@ class HierAvg:
             return out
         import torch
         out = torch.empty((self.P, self.D), dtype=torch.float32, device=device)
+        # The memory may be reused from a tensor that torch's stream still
+        # works on; the handle writes on its own stream.
+        torch.cuda.current_stream(out.device).synchronize()
         self.params_into(out.data_ptr(), out.numel())
         return out
 
