@@ -105,6 +105,7 @@ struct hieravg {
   bool rows_stale = false;  // replicas 1..P-1 hold an old W1 (after a delayed round);
                             // averaging kind: every row is old, Wm holds the parameters
   bool in_shared = false;   // averaging kind: the round being enqueued starts from Wm
+  bool avg_round = false;   // averaging kind: one pass takes all steps of a round
   bool fused = false;       // the fused step kernel applies (SG = 1)
   bool fused_mean = false;  // ... and also with the cluster mean (SG = S)
   int KS_step = 1, KS_mean = 1;  // forward splits written by the fused kernel
@@ -479,6 +480,7 @@ int build(hieravg* h) {
     h->D = c.in_dim;
     h->Dp = round_up(h->D, 64);
     const int T = h->T;
+    h->avg_round = T >= 2 && avg_round_supported(c.S);
     int rc;
     if ((rc = alloc_zero(h, (void**)&h->W, sizeof(float) * P * h->Dp, "replicas"))) return rc;
     if ((rc = alloc_zero(h, (void**)&h->V, sizeof(float) * P * h->Dp, "momentum buffers"))) return rc;
@@ -657,6 +659,27 @@ bool launch_class(hieravg* h, int kc, int tt) {
   float* W = h->W;
   if (c.kind == HIERAVG_KIND_AVERAGING) {
     const float* g = h->Gr + (int64_t)tt * P * h->Dp;
+    if (h->avg_round) {
+      // Every step of the round in one launch (from Wm, or from every row),
+      // the clusters' means to their first rows; then their mean to Wm.  One
+      // cluster writes Wm itself (one learner its row).
+      const bool one = P == S;
+      switch (kc) {
+        case KC_MOMENTUM_FIRST:
+        case KC_MOMENTUM_GROUP:
+          if ((kc == KC_MOMENTUM_FIRST) != h->in_shared) return false;
+          launch_avg_round(s, h->in_shared ? h->Wm : W, h->in_shared ? 0 : h->Dp, h->V, h->Gr, h->Dp, P, S, h->T,
+                           c.K1, h->hyper, c.momentum, c.weight_decay, c.avg_momentum != 0,
+                           one && P > 1 ? h->Wm : W, (int64_t)S * h->Dp);
+          return true;
+        case KC_MOMENTUM_GLOBAL:
+          if (one) return false;
+          launch_mean_rows(s, h->Wm, W, (int64_t)S * h->Dp, h->Dp, P / S);
+          return true;
+        case KC_VMEAN_GLOBAL: launch_group_mean(s, h->V, h->Dp, h->Dp, P, P); return true;
+        default: return false;
+      }
+    }
     switch (kc) {
       case KC_MOMENTUM:
         launch_momentum_step(s, W, h->V, g, h->Dp, P, 1, false, h->hyper, c.momentum, c.weight_decay);
@@ -1360,6 +1383,13 @@ void enqueue_round(hieravg* h) {
   const int T = h->T;
   const int P = c.P;
   if (c.kind == HIERAVG_KIND_AVERAGING) {
+    auto go = [&](int kc) { run(h, kc, [&] { launch_class(h, kc, 0); }); };
+    if (h->avg_round) {
+      go(h->in_shared ? KC_MOMENTUM_FIRST : KC_MOMENTUM_GROUP);
+      if (P > c.S) go(KC_MOMENTUM_GLOBAL);
+      if (P > 1 && c.avg_momentum) go(KC_VMEAN_GLOBAL);
+      return;
+    }
     // The first step reads every learner's parameters from Wm when the round
     // starts from a common value; the global mean writes Wm.
     for (int tt = 0; tt < T; ++tt) {

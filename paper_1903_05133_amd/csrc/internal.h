@@ -551,6 +551,15 @@ void launch_momentum_step(hipStream_t s, float* W, float* V, const float* Gr, in
                           bool average, const float* lr, float mu, float wd, const float* shared_in = nullptr,
                           float* mean_out = nullptr);
 
+// Averaging kind: all T steps of a round in one pass (avg_round_supported(S)),
+// with the cluster means every K1 steps but the last (avg_v: the buffers' too)
+// in it; the clusters' means at the round's end go to M, mp floats apart.
+// W: learner 0's parameters, w_pitch apart (0: one vector for all); Gr:
+// [T][P][Dp].  M may be W with mp = S * w_pitch.
+bool avg_round_supported(int S);
+void launch_avg_round(hipStream_t s, const float* W, int64_t w_pitch, float* V, const float* Gr, int64_t Dp, int P,
+                      int S, int T, int K1, const float* lr, float mu, float wd, bool avg_v, float* M, int64_t mp);
+
 // The replica rows of P learners to a dense [P][D] array in device memory:
 // per parameter block, `rows` rows of `cols` floats, ld floats apart at
 // src + p*pitch (pitch 0: one copy for every learner), to offset `off` of
