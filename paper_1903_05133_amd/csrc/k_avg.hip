@@ -302,38 +302,39 @@ void launch_momentum_step(hipStream_t s, float* W, float* V, const float* Gr, in
 // W: every row of a column is read before it is written.  HBM-bound: per column
 // and learner 4 T bytes of gradients and 8 of buffers, where a pass per step
 // moves 16 to 20 T.  The next step's gradients are in flight during a step.
-// 32 replicas of 11.7M floats, S = 4, T = 4: 4.55 ms a round in four passes,
-// 2.0 ms in one (9.4 GB).
-template <int S, int V>
+// One float per thread: narrow row segments in many waves (32 x 11.7M, S = 4,
+// T = 4: 1.78 ms = 5.3 TB/s, 1.87 with 16-byte pieces; plain loads, 12 x 1M,
+// S = 3, T = 6: 60 us, 68 with non-temporal ones).  The round went from 4.55 ms
+// in four passes to 1.86.
+template <int S>
 __global__ __launch_bounds__(256) void k_avg_round(const float* Wsrc, int64_t wp, float* __restrict__ Vb,
                                                    const float* __restrict__ Gr, int64_t pitch, int P, int T, int K1,
                                                    const float* __restrict__ lr_ptr, float mu, float wd, bool avg_v,
                                                    float* M, int64_t mp) {
-  typedef float vec __attribute__((ext_vector_type(V)));
   const int64_t i = blockIdx.x * 256ll + threadIdx.x;
-  if (i >= pitch / V) return;
+  if (i >= pitch) return;
   const float lr = *lr_ptr;
   const int64_t row0 = (int64_t)blockIdx.y * S;
-  vec w[S], v[S], g[2][S];
-  auto load = [&](int tt, vec (&d)[S]) {
+  float w[S], v[S], g[2][S];
+  auto load = [&](int tt, float (&d)[S]) {
     const float* b = Gr + ((int64_t)min(tt, T - 1) * P + row0) * pitch;  // past the end: the last step again, unused
 #pragma unroll
-    for (int u = 0; u < S; ++u) d[u] = __builtin_nontemporal_load((const vec*)(b + u * pitch) + i);
+    for (int u = 0; u < S; ++u) d[u] = b[u * pitch + i];
   };
   load(0, g[0]);
 #pragma unroll
   for (int u = 0; u < S; ++u) {
-    v[u] = __builtin_nontemporal_load((const vec*)(Vb + (row0 + u) * pitch) + i);
-    w[u] = __builtin_nontemporal_load((const vec*)(Wsrc + (row0 + u) * wp) + i);
+    v[u] = Vb[(row0 + u) * pitch + i];
+    w[u] = Wsrc[(row0 + u) * wp + i];
   }
-  auto mean = [&](vec (&x)[S]) {
-    vec sum = x[0];
+  auto mean = [&](float (&x)[S]) {
+    float sum = x[0];
 #pragma unroll
     for (int u = 1; u < S; ++u) sum += x[u];
     return (S & (S - 1)) == 0 ? sum * (1.0f / (float)S) : sum / (float)S;
   };
   int left = K1;  // steps to the block's end
-  auto step = [&](int tt, vec (&gc)[S]) {
+  auto step = [&](int tt, float (&gc)[S]) {
 #pragma unroll
     for (int u = 0; u < S; ++u) {
       v[u] = mu * v[u] + (gc[u] + wd * w[u]);
@@ -342,11 +343,11 @@ __global__ __launch_bounds__(256) void k_avg_round(const float* Wsrc, int64_t wp
     if (--left == 0) {
       left = K1;
       if (S > 1 && tt != T - 1) {  // the round's last step takes the global mean
-        const vec m = mean(w);
+        const float m = mean(w);
 #pragma unroll
         for (int u = 0; u < S; ++u) w[u] = m;
         if (avg_v) {
-          const vec n = mean(v);
+          const float n = mean(v);
 #pragma unroll
           for (int u = 0; u < S; ++u) v[u] = n;
         }
@@ -363,8 +364,8 @@ __global__ __launch_bounds__(256) void k_avg_round(const float* Wsrc, int64_t wp
     step(tt + 1, g[1]);
   }
 #pragma unroll
-  for (int u = 0; u < S; ++u) __builtin_nontemporal_store(v[u], (vec*)(Vb + (row0 + u) * pitch) + i);
-  __builtin_nontemporal_store(mean(w), (vec*)(M + (int64_t)blockIdx.y * mp) + i);
+  for (int u = 0; u < S; ++u) __builtin_nontemporal_store(v[u], Vb + (row0 + u) * pitch + i);
+  __builtin_nontemporal_store(mean(w), M + (int64_t)blockIdx.y * mp + i);
 }
 
 // Cluster sizes whose columns fit in registers; the others take a pass per step.
@@ -372,20 +373,20 @@ bool avg_round_supported(int S) { return (S >= 1 && S <= 8) || S == 16 || S == 3
 
 void launch_avg_round(hipStream_t s, const float* W, int64_t w_pitch, float* V, const float* Gr, int64_t Dp, int P,
                       int S, int T, int K1, const float* lr, float mu, float wd, bool avg_v, float* M, int64_t mp) {
-#define HAV_AR(S_, V_)                                                                                          \
-  launch(k_avg_round<S_, V_>, dim3((unsigned)((Dp / V_ + 255) / 256), (unsigned)(P / S)), 256, 0, s, W, w_pitch, V, \
+#define HAV_AR(S_)                                                                                              \
+  launch(k_avg_round<S_>, dim3((unsigned)((Dp + 255) / 256), (unsigned)(P / S)), 256, 0, s, W, w_pitch, V, \
          Gr, Dp, P, T, K1, lr, mu, wd, avg_v, M, mp)
   switch (S) {
-    case 1: HAV_AR(1, 4); break;
-    case 2: HAV_AR(2, 4); break;
-    case 3: HAV_AR(3, 4); break;
-    case 4: HAV_AR(4, 4); break;
-    case 5: HAV_AR(5, 4); break;
-    case 6: HAV_AR(6, 4); break;
-    case 7: HAV_AR(7, 4); break;
-    case 8: HAV_AR(8, 4); break;
-    case 16: HAV_AR(16, 2); break;
-    default: HAV_AR(32, 1); break;
+    case 1: HAV_AR(1); break;
+    case 2: HAV_AR(2); break;
+    case 3: HAV_AR(3); break;
+    case 4: HAV_AR(4); break;
+    case 5: HAV_AR(5); break;
+    case 6: HAV_AR(6); break;
+    case 7: HAV_AR(7); break;
+    case 8: HAV_AR(8); break;
+    case 16: HAV_AR(16); break;
+    default: HAV_AR(32); break;
   }
 #undef HAV_AR
 }

@@ -1014,3 +1014,32 @@ def test_forced_allocation_failures_leave_no_broken_state(gpu_lib, monkeypatch):
     monkeypatch.delenv("HIERAVG_FAIL_ALLOC")
     got, idx, _ = _run_gpu(c)
     _check(c, got, idx, *_oracle(c))
+
+
+# ------------------------------------------------- averaging: one pass a round
+@pytest.mark.parametrize("P,S,K1,T", [(1, 1, 2, 3), (2, 1, 1, 2), (4, 4, 3, 5), (6, 3, 2, 4), (14, 7, 1, 3), (16, 8, 4, 4),
+                                      (32, 16, 1, 2), (32, 32, 3, 7), (18, 9, 2, 3), (4, 2, 2, 1)])
+@pytest.mark.parametrize("avg_momentum", [False, True])
+def test_averaging_rounds_of_every_cluster_size(P, S, K1, T, avg_momentum, gpu_lib):
+    """Every cluster size of the one-pass round, sizes past it (S = 9) and
+    rounds of one step (a pass per step), whole and cut blocks, buffers kept
+    and averaged: three rounds against the oracle, the second from rows that
+    differ."""
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("averaging", P, S, K1, 1, IN=301, lr=0.1, momentum=0.9, weight_decay=0.01, k_global=T,
+                   avg_momentum=avg_momentum, seed=400 + S)
+    print(f"[gpu case] {c}", flush=True)
+    prob = cases.oracle_problem(c)
+    st = M.create(prob)
+    with HierAvg(config=cases.native_config(c)) as h:
+        for r in range(3):
+            if r == 1:
+                w = h.params()
+                w += np.arange(P, dtype=np.float32)[:, None] * 0.01
+                h.set_params(w)
+                st.W = w.astype(np.float64)
+            h.round()
+            M.hieravg_round(prob, st)
+            for arr, want in ((h.params(), st.W), (h.momentum(), st.V)):
+                ok, det = cases.parity_report(prob, arr, want)
+                assert ok, (r, det)
