@@ -76,7 +76,10 @@ typedef struct hieravg* hieravg_t;
  *           pair plus weighted sums of the step gradients, and the block end
  *           applies those weights in the same cluster GEMM.
  *  AUTO:    DELAYED where it applies and its extra Gram products cost at most
- *           an eighth of the step's flops ((K1 - 1) * B <= H / 2), else EAGER.
+ *           an eighth of the step's flops ((K1 - 1) * B <= H / 2); also, with
+ *           plain SGD, for 32 < B <= 128 where (K1 - 1) * B <= H and W1 holds
+ *           2^19 floats or more (B, H, W1 padded to 16, 64, 64 x 64); else
+ *           EAGER.
  */
 #define HIERAVG_UPDATE_AUTO 0
 #define HIERAVG_UPDATE_EAGER 1

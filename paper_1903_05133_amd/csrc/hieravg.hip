@@ -20,7 +20,8 @@
 //    the remaining parameters.  Only step 0 of a round runs the stand-alone
 //    forward kernel, and the last step the plain update before the global
 //    mean.
-//  - delayed (MLP): within a block the first weight block of every learner of
+//  - delayed (MLP; minibatches up to 32, and under AUTO up to 128 where it
+//    pays): within a block the first weight block of every learner of
 //    a cluster is the cluster's block-start copy minus the rank-B updates of
 //    its earlier steps, so one GEMM per cluster gives the forward of all K1
 //    steps (plus Gram corrections), and one GEMM per cluster at the block end
@@ -55,7 +56,7 @@ const char* kClassNames[KC_COUNT] = {
     "w1_global_mean", "tail_global_mean", "gram_reduce", "head_step", "head_step_end",
     "z1_delayed", "momentum_buffer_group_mean", "momentum_buffer_global_mean", "momentum_first_step",
     "fwd1_block_gemm_v", "scale_errors", "buffer_update_gemm", "update1_gemm_group_mean", "fwd1_group_gemm",
-    "update1_gemm_global_mean", "head_fused", "head_w2_step"};
+    "update1_gemm_global_mean", "head_fused", "head_w2_step", "b1_step"};
 
 struct ProfRec {
   hipEvent_t a, b;
@@ -137,6 +138,7 @@ struct hieravg {
   // Delayed first-layer updates (see hieravg.h, HIERAVG_UPDATE_DELAYED).
   bool delayed = false;    // the handle uses them for rounds that start with equal W1
   bool global_last = false; // the last block's update takes the global mean (K1*P*B rows fit)
+  bool wide = false;        // delayed updates with minibatches of 33 to 128 samples (AUTO only)
   bool hb = false;          // delayed updates with momentum or weight decay (heavy-ball blocks)
   int KSv = 1, cpsv = 1;    // splits of the block-wide forward from the learners' buffers
   float* partv = nullptr;   // [KSv][K1][P][Bp][Hp] partials of X_k V^T (momentum > 0)
@@ -332,6 +334,25 @@ int validate(const hieravg_config& c) {
   return HIERAVG_OK;
 }
 
+// Minibatches of 33 to 128 samples under AUTO (plain SGD): the delayed schedule
+// with the head kernels of the eager one, the Gram blocks as a split product
+// and the correction as a kernel of its own.  Where the Gram work stays below
+// about half of the step's ((K1 - 1) * B <= H) and W1 is large enough for its
+// traffic to count: an eager step reads and writes every learner's W1, or, past
+// the fused step (B > 64), runs it through an update and a forward.  Figures
+// of a round, eager and delayed: 64 learners of 3072-512-10, 8 x 64 samples a
+// block: 8.8 ms and 4.3; 8 learners of 3072-512-100, 4 x 128: 1.18 ms (1.53 before the split
+// products) and 0.81.
+bool wide_applies(const hieravg* h, int B) {
+  const hieravg_config& c = h->cfg;
+  const int64_t Bp = round_up(B, 16);
+  return B > 32 && B <= 128 && c.K1 <= 8 && c.k_global % c.K1 == 0 && c.momentum == 0.0f && c.weight_decay == 0.0f &&
+         c.avg_momentum == 0 && (int64_t)c.K1 * c.S * B <= kBlkMaxRows &&
+         (double)h->N * (double)h->INp < 274877906944.0 && (c.classes > kSmallC || h->head_fused) &&
+         (c.K1 - 1) * Bp <= h->Hp && h->Hp * h->INp >= (1 << 19) &&
+         (double)c.K2 * c.P * c.K1 * c.K1 * Bp * Bp * sizeof(float) <= 2e9;
+}
+
 float fan_in_scale(int64_t fan_in) { return (float)(1.0 / std::sqrt((double)fan_in)); }
 
 // Launch plan for minibatch size B (softmax / MLP kinds): padded batch,
@@ -384,6 +405,10 @@ int64_t plan(hieravg* h, int B) {
     const bool cheap = (int64_t)(c.K1 - 1) * h->Bp * 2 <= h->Hp;
     h->delayed = c.update_mode == HIERAVG_UPDATE_DELAYED || (c.update_mode == HIERAVG_UPDATE_AUTO && cheap);
   }
+  h->wide = mlp && !h->delayed && c.update_mode == HIERAVG_UPDATE_AUTO && wide_applies(h, B);
+  h->delayed = h->delayed || h->wide;
+  h->KSG = !h->delayed ? 1 : h->wide ? gram_split_splits(P, c.K1, c.K2, h->Bp, (int)h->INp)
+                                     : gram_splits(P, c.K2, (int)h->INp);
   // The last block's update over all P learners has one group of output
   // tiles (64 x 128); with fewer than two per CU the G cluster updates and a
   // separate mean of the copies fill the GPU better.  Heavy-ball blocks with
@@ -520,6 +545,7 @@ int build(hieravg* h) {
     int64_t part_floats = 0, part2_floats = 0, partv_floats = 0;
     bool any_delayed = false, any_hb = false, any_once = false;
     int Bp_del = 0;
+    int64_t gram_floats = 0;
     for (int b = 16; b <= round_up(c.B, 16); b += 16) {
       const int64_t pf = plan(h, std::min(b, c.B));
       part_floats = std::max(part_floats, pf);
@@ -528,6 +554,8 @@ int build(hieravg* h) {
         any_delayed = true;
         any_hb = any_hb || h->hb;
         Bp_del = std::max(Bp_del, h->Bp);
+        gram_floats = std::max<int64_t>(gram_floats,
+                                        (int64_t)h->KSG * c.K2 * P * c.K1 * c.K1 * h->Bp * h->Bp);
         part2_floats = std::max<int64_t>(part2_floats, (int64_t)h->KS2 * P * h->Bp * h->Cp);
         if (h->hb) partv_floats = std::max<int64_t>(partv_floats, (int64_t)h->KSv * c.K1 * P * h->Bp * h->Hp);
       }
@@ -595,10 +623,7 @@ int build(hieravg* h) {
       if (h->C > kSmallC &&
           (rc = alloc_zero(h, (void**)&h->part2, sizeof(float) * part2_floats, "layer-2 partials")))
         return rc;
-      h->KSG = gram_splits(P, c.K2, (int)h->INp);
-      if (c.K1 > 1 && (rc = alloc_zero(h, (void**)&h->gram,
-                                       sizeof(float) * h->KSG * c.K2 * P * c.K1 * c.K1 * Bp_del * Bp_del, "Gram blocks")))
-        return rc;
+      if (c.K1 > 1 && (rc = alloc_zero(h, (void**)&h->gram, sizeof(float) * gram_floats, "Gram blocks"))) return rc;
     }
     plan(h, c.B);  // again, now that the buffers of the once-written means exist
     h->key_index = hash64(seed, kTagIndex);
@@ -839,7 +864,10 @@ bool launch_class(hieravg* h, int kc, int tt) {
     case KC_TAIL_GLOBAL: launch_group_mean(s, W + h->off_b1, h->Dp, h->Dp - h->off_b1, P, P); return true;
     case KC_GRAM:
       if (!h->delayed || h->gram == nullptr) return false;
-      launch_gram(s, h->X, h->INp, INp, h->idx, h->gram, P, c.K1, c.K2, B, Bp, h->KSG);
+      if (h->wide)
+        launch_gram_split(s, h->X, h->INp, INp, h->idx, h->gram, P, c.K1, c.K2, B, Bp, h->KSG, x_exp(h));
+      else
+        launch_gram(s, h->X, h->INp, INp, h->idx, h->gram, P, c.K1, c.K2, B, Bp, h->KSG);
       return true;
     case KC_GRAM_REDUCE:
       if (!h->delayed || h->gram == nullptr || h->KSG < 2) return false;
@@ -998,8 +1026,8 @@ bool launch_class(hieravg* h, int kc, int tt) {
       return true;
     }
     case KC_HEAD_FUSED:
-    case KC_HEAD_W2: {  // eager schedule
-      if (!small || h->in_delayed || !h->head_fused) return false;
+    case KC_HEAD_W2: {  // eager schedule, or delayed with more than 32 samples
+      if (!small || (h->in_delayed && !h->wide) || !h->head_fused) return false;
       HeadFusedArgs a;
       a.part = h->part;
       a.KS = h->ks_cur;
@@ -1026,6 +1054,20 @@ bool launch_class(hieravg* h, int kc, int tt) {
         a.mom.vb2 = h->V + h->off_b2;
       }
       a.scratch = h->hgrad;
+      if (h->in_delayed) {
+        // step 0 of a block reads the block forward's partials, the others the
+        // corrected sums; the errors are kept for the block end
+        const int k = tt % c.K1;
+        if (k == 0) {
+          a.split = (int64_t)c.K1 * P * Bp * Hp;
+        } else {
+          a.part = h->Z1;
+          a.KS = 1;
+        }
+        a.G1 = h->Gs + (int64_t)k * P * Bp * Hp;
+        a.gmax = mag_tables(h).g + (int64_t)(tt / c.K1) * (P / S) * Hp;
+        a.gS = S;
+      }
       if (kc == KC_HEAD_FUSED)
         launch_head_fused(s, a);
       else
@@ -1093,7 +1135,10 @@ bool launch_class(hieravg* h, int kc, int tt) {
     }
     case KC_BWD_HIDDEN:
       if (small) return false;
-      if (h->in_delayed)  // the hidden errors are kept for the block end; b1 takes its step here
+      if (h->in_delayed && h->wide)  // b1 takes its step in KC_B1_STEP
+        launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->Gs + (int64_t)(tt % c.K1) * P * Bp * Hp, P, B,
+                          Bp, C, Cp, Hp);
+      else if (h->in_delayed)  // the hidden errors are kept for the block end; b1 takes its step here
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->Gs + (int64_t)(tt % c.K1) * P * Bp * Hp, P, B,
                           Bp, C, Cp, Hp, W + h->off_b1, h->hyper, h->hb && h->V ? h->V + h->off_b1 : nullptr,
                           h->hb ? c.momentum : 0.0f, h->hb ? c.weight_decay : 0.0f,
@@ -1105,8 +1150,13 @@ bool launch_class(hieravg* h, int kc, int tt) {
       else
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->G1, P, B, Bp, C, Cp, Hp);
       return true;
+    case KC_B1_STEP:
+      if (!h->in_delayed || !h->wide || small) return false;
+      launch_b1_step(s, h->Gs + (int64_t)(tt % c.K1) * P * Bp * Hp, W + h->off_b1, h->Dp, h->hyper, P, B, Bp, Hp,
+                     mag_tables(h).g + (int64_t)(tt / c.K1) * (P / S) * Hp, S);
+      return true;
     case KC_Z1_DELAYED: {
-      if (!h->in_delayed || small) return false;
+      if (!h->in_delayed || (small && !h->wide)) return false;
       Z1Args a{};
       const int k = tt % c.K1;
       a.part = h->part + (int64_t)k * P * Bp * Hp;
@@ -1132,7 +1182,10 @@ bool launch_class(hieravg* h, int kc, int tt) {
           a.splitv = (int64_t)c.K1 * P * Bp * Hp;
         }
       }
-      launch_z1_delayed(s, a);
+      if (h->wide)
+        launch_z1_wide(s, a, !small);
+      else
+        launch_z1_delayed(s, a);
       return true;
     }
     case KC_UPDATE2: {
@@ -1417,7 +1470,16 @@ void enqueue_round(hieravg* h) {
     for (int b = 0; b < c.K2; ++b) {
       go(KC_FWD1_BLOCK, b * c.K1);
       if (h->hb && h->V) go(KC_FWD1_BLOCK_V, b * c.K1);  // heavy-ball: X_k V^T of every learner
-      if (h->C <= kSmallC) {
+      if (h->wide) {  // more than 32 samples: the eager heads on corrected sums, per step
+        for (int k = 0; k < c.K1; ++k) {
+          const int tt = b * c.K1 + k;
+          if (k > 0 || h->C > kSmallC) go(KC_Z1_DELAYED, tt);
+          if (h->C <= kSmallC)
+            for (int kc : {KC_HEAD_FUSED, KC_HEAD_W2}) go(kc, tt);
+          else
+            for (int kc : {KC_FWD2, KC_SOFTMAX, KC_BWD_HIDDEN, KC_B1_STEP, KC_UPDATE2}) go(kc, tt);
+        }
+      } else if (h->C <= kSmallC) {
         for (int k = 0; k < c.K1; ++k) go(KC_HEAD_STEP, b * c.K1 + k);
         go(KC_HEAD_END, b * c.K1 + c.K1 - 1);
       } else {  // more than 32 classes: the layer-2 GEMMs of the eager head, per step

@@ -141,6 +141,7 @@ enum KernelClass {
   KC_UPD1_GLOBAL,    // layer-1 update of every learner with the global mean (a round's last step)
   KC_HEAD_FUSED,     // small C, eager: the loss side of a step (G1, gradient rows of W2, b1, b2)
   KC_HEAD_W2,        // small C, eager: the step of W2, b1, b2 from those rows
+  KC_B1_STEP,        // delayed updates, more than 32 classes and samples: the step of b1
   KC_COUNT
 };
 
@@ -358,6 +359,11 @@ void launch_block_update(hipStream_t s, const BlkArgs& a);
 int gram_splits(int P, int K2, int K);
 void launch_gram(hipStream_t s, const float* X, int64_t ldx, int K, const int32_t* idx, float* gram, int P,
                  int K1, int K2, int B, int Bp, int KSG);
+// The same blocks for any padded minibatch (K a multiple of 64; xexp as in
+// FwdArgs), and its split count.
+int gram_split_splits(int P, int K1, int K2, int Bp, int K);
+void launch_gram_split(hipStream_t s, const float* X, int64_t ldx, int K, const int32_t* idx, float* gram, int P,
+                       int K1, int K2, int B, int Bp, int KSG, int xexp);
 void launch_gram_reduce(hipStream_t s, float* gram, int P, int K1, int K2, int Bp, int KSG);
 
 // Fused step of the first weight block: the update of step t (Bsrc = the
@@ -441,6 +447,13 @@ struct Z1Args {
   int64_t splitv = 0;
 };
 void launch_z1_delayed(hipStream_t s, const Z1Args& a);
+// The same for any M, plain SGD (K1 <= 8); bias: b1 is added (else the result
+// takes the place of one split's partial sums).
+void launch_z1_wide(hipStream_t s, const Z1Args& a, bool bias);
+// b1 -= lr * the column sums of G1 ([P][Mp][Hp], M rows), gmax ([P/gS][Hp])
+// raised to the units' largest errors.
+void launch_b1_step(hipStream_t s, const float* G1, float* b1, int64_t w_pitch, const float* lr, int P, int M, int Mp,
+                    int Hp, uint32_t* gmax, int gS);
 // part_split: floats between split-K partial sums (0: P * Mp * Hp).
 void launch_head_a(hipStream_t s, const float* part, int KS, const float* b1, const float* W2, const float* b2,
                    int64_t w_pitch, float* Z1, float* PL, int P, int M, int Mp, int C, int Cp, int Hp,
@@ -474,6 +487,8 @@ struct HeadFusedArgs {
   int P = 0, M = 0, Mp = 0, C = 0, Cp = 0, Hp = 0;
   const float* lr = nullptr;
   HeadMom mom;
+  uint32_t* gmax = nullptr;  // optional, [P/gS][Hp]: raised to each unit's largest error over a cluster
+  int gS = 1;
   float* scratch = nullptr;  // head_fused_scratch_floats(P, Mp, C, Hp) floats
 };
 bool head_fused_supported(int Hp, int Cp);

@@ -506,6 +506,97 @@ __global__ __launch_bounds__(256) void k_z1_delayed(Z1Args a, int htiles) {
   if (rr < M) *(f32x4*)(a.Z1 + ((int64_t)p * Mp + rr) * Hp + h4) = z;
 }
 
+// The same for any padded minibatch (a multiple of 16), plain SGD: workgroup
+// (learner, 32 samples, 32 hidden units), the correction's k * Mp terms split
+// over its four waves as 32x32x2 MFMAs whose operands come straight from
+// memory (both are read by few workgroups): lane (l, h) takes the Gram piece
+// [l][8q + 4h ..+3] and the errors of those four samples.  bias: b1 is added.
+__global__ __launch_bounds__(256) void k_z1_wide(Z1Args a, int htiles, int mtiles, bool bias) {
+  __shared__ float cbuf[4][32][33];
+  const int ht = blockIdx.x % htiles, mt = blockIdx.x / htiles % mtiles, p = blockIdx.x / (htiles * mtiles);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+  const int M = a.M, Mp = a.Mp, Hp = a.Hp;
+  const int u4 = tid & 7, rr = 32 * mt + (tid >> 3), h4 = 32 * ht + 4 * u4;
+  const float* pm = a.part + ((int64_t)p * Mp + min(rr, M - 1)) * Hp + h4;
+  f32x4 z = *(const f32x4*)pm;
+#pragma unroll 4
+  for (int ks = 1; ks < a.KS; ++ks) z += *(const f32x4*)(pm + ks * a.split);
+  if (a.k > 0) {
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    const int row = min(32 * mt + l32, Mp - 1), nq = a.k * Mp / 8;
+    const float* gr = a.gram + (((int64_t)p * a.K1 + a.k) * a.K1) * Mp * Mp + (int64_t)row * Mp + 4 * lhi;
+    const float* gs = a.gs + (int64_t)p * Mp * Hp + 32 * ht + l32;
+    const float inv = qdiv_inv(Mp);
+#pragma unroll 4
+    for (int q = wave; q < nq; q += 4) {
+      const int k2 = qdiv_small(8 * q, Mp, inv), s0 = 8 * q - k2 * Mp;
+      const f32x4 x = *(const f32x4*)(gr + (int64_t)k2 * Mp * Mp + s0);
+      const float* e0 = gs + (int64_t)k2 * a.P * Mp * Hp;
+      float y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int s2 = s0 + 4 * lhi + e;
+        y[e] = e0[(int64_t)min(s2, M - 1) * Hp];  // past M: a Gram column of zeros meets it
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) cbuf[wave][8 * (r >> 2) + 4 * lhi + (r & 3)][l32] = acc[r];
+    __syncthreads();
+    f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float* cr = &cbuf[w][tid >> 3][4 * u4];
+      c += f32x4{cr[0], cr[1], cr[2], cr[3]};
+    }
+    z -= *a.lr * c;
+  }
+  if (bias) z += *(const f32x4*)(a.b1 + (int64_t)p * a.w_pitch + h4);
+  if (rr < M) *(f32x4*)(a.Z1 + ((int64_t)p * Mp + rr) * Hp + h4) = z;
+}
+
+void launch_z1_wide(hipStream_t s, const Z1Args& a, bool bias) {
+  const int htiles = a.Hp / 32, mtiles = (a.M + 31) / 32;
+  launch(k_z1_wide, a.P * mtiles * htiles, 256, 0, s, a, htiles, mtiles, bias);
+}
+
+// b1 -= lr * sum_m G1[m], and the units' largest errors into gmax, for
+// minibatches whose hidden errors several workgroups write: workgroup
+// (learner, 64 units), four threads per unit.
+__global__ __launch_bounds__(256) void k_b1_step(const float* __restrict__ G1, float* __restrict__ b1, int64_t w_pitch,
+                                                 const float* __restrict__ lr, int M, int Mp, int Hp, int htiles,
+                                                 uint32_t* __restrict__ gmax, int gS) {
+  __shared__ float ps[4][64];
+  __shared__ uint32_t pm[4][64];
+  const int p = blockIdx.x / htiles, u = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int h = (blockIdx.x % htiles) * 64 + u;
+  const float* src = G1 + (int64_t)p * Mp * Hp + h;
+  float sum = 0.0f;
+  uint32_t mag = 0;
+#pragma unroll 8
+  for (int m = g; m < M; m += 4) {
+    const float v = src[(int64_t)m * Hp];
+    sum += v;
+    mag = max(mag, __builtin_bit_cast(uint32_t, v) & 0x7fffffffu);
+  }
+  ps[g][u] = sum;
+  pm[g][u] = mag;
+  __syncthreads();
+  if (g == 0) {
+    float* b = b1 + (int64_t)p * w_pitch + h;
+    *b -= *lr * ((ps[0][u] + ps[1][u]) + (ps[2][u] + ps[3][u]));
+    atomicMax(gmax + (int64_t)(p / gS) * Hp + h, max(max(pm[0][u], pm[1][u]), max(pm[2][u], pm[3][u])));
+  }
+}
+
+void launch_b1_step(hipStream_t s, const float* G1, float* b1, int64_t w_pitch, const float* lr, int P, int M, int Mp,
+                    int Hp, uint32_t* gmax, int gS) {
+  launch(k_b1_step, P * (Hp / 64), 256, 0, s, G1, b1, w_pitch, lr, M, Mp, Hp, Hp / 64, gmax, gS);
+}
+
 void launch_z1_delayed(hipStream_t s, const Z1Args& a) {
   const int htiles = a.Hp / 32;
   launch(k_z1_delayed, a.P * htiles, 256, 0, s, a, htiles);
@@ -906,11 +997,18 @@ __global__ __launch_bounds__(64 * kHfWaves) void k_head_fused(HeadFusedArgs a) {
                                                       fmaxf(zs[(4 * t + lg) * kZL + u], 0.0f), d2[ct], 0, 0, 0);
     }
     float db1 = 0.0f;
+    uint32_t mag = 0;  // bits of the largest error (NaN and infinity above all)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float g = zs[(4 * lg + r) * kZL + u] > 0.0f ? d1[r] : 0.0f;
       g1[(int64_t)(4 * lg + r) * Hp + u] = g;
       db1 += g;
+      mag = max(mag, __builtin_bit_cast(uint32_t, g) & 0x7fffffffu);
+    }
+    if (a.gmax) {
+      mag = max(mag, (uint32_t)__shfl_xor((int)mag, 16, 64));
+      mag = max(mag, (uint32_t)__shfl_xor((int)mag, 32, 64));
+      if (lg == 0) atomicMax(a.gmax + (int64_t)(p / a.gS) * Hp + u, mag);
     }
     db1 += __shfl_xor(db1, 16, 64);
     db1 += __shfl_xor(db1, 32, 64);

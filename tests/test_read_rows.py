@@ -35,7 +35,7 @@ def test_device_reads_equal_host_reads(name, offset, gpu_lib):
             w = h.params()
             h.set_params(w + np.arange(c["P"], dtype=np.float32)[:, None])
         n = c["P"] * h.D
-        buf = torch.full((n + 8,), 7.0, device="cuda")
+        buf = torch.full((n + 8,), 7.0, dtype=torch.float32, device="cuda")
         torch.cuda.synchronize()  # the handle reads on a stream of its own
         h.params_into(buf.data_ptr() + 4 * offset, n)
         got = buf.cpu().numpy()

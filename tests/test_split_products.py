@@ -39,6 +39,14 @@ TILES = {
     # 128 x 128 block-update tiles, ragged (320 units, 3008 features)
     "delayed_update_128": (cases.case("mlp", 16, 4, 2, 2, B=9, IN=3001, H=310, C=5, N=300, sigma=0.5, lr=0.05, seed=208),
                            "delayed"),
+    # more than 32 samples under AUTO (W1 of 2^19 and more, (K1 - 1) * B <= H):
+    # whole and ragged minibatches (Gram tiles across steps), both heads, one
+    # step per block, the Gram blocks in feature splits
+    "wide_64": (cases.case("mlp", 4, 2, 4, 2, B=64, IN=2048, H=256, C=7, N=300, sigma=0.5, lr=0.02, seed=221), "auto"),
+    "wide_40": (cases.case("mlp", 6, 3, 3, 2, B=40, IN=1900, H=300, C=20, N=300, sigma=0.5, lr=0.02, seed=222), "auto"),
+    "wide_100_c50": (cases.case("mlp", 4, 2, 3, 2, B=100, IN=2100, H=250, C=50, N=300, sigma=0.5, lr=0.02, seed=223), "auto"),
+    "wide_128_c33": (cases.case("mlp", 2, 1, 2, 1, B=128, IN=4096, H=128, C=33, N=300, sigma=0.5, lr=0.02, seed=224), "auto"),
+    "wide_one_step": (cases.case("mlp", 4, 4, 1, 2, B=33, IN=3000, H=192, C=3, N=300, sigma=0.5, lr=0.02, seed=225), "auto"),
     # one step per block, one sample: the shortest contractions
     "delayed_one_sample": (cases.case("mlp", 2, 1, 1, 2, B=1, IN=64, H=64, C=3, N=30, lr=0.1, seed=209), "delayed"),
 }
@@ -50,6 +58,33 @@ def test_tiles_match_oracle(name, gpu_lib):
     rounds = 1 if name == "delayed_256" else 2
     got, idx, _ = _run_gpu(c, rounds, mode)
     _check(c, got, idx, *_oracle(c, rounds), mode=mode)
+
+
+@pytest.mark.parametrize("name", [n for n in sorted(TILES) if n.startswith("wide")])
+def test_wide_minibatch_schedule(name, gpu_lib):
+    """AUTO takes the delayed schedule for these; set_batch moves the handle
+    between it, the 32-sample form and eager rounds."""
+    from paper_1903_05133_amd import HierAvg
+    from dataclasses import replace
+    c, _ = TILES[name]
+    prob = cases.oracle_problem(c)
+    st = M.create(prob)
+    print(f"[gpu case] schedule {c}", flush=True)
+    with HierAvg(config=cases.native_config(c)) as h:
+        for B in (c["B"], 20, c["B"] - 1):
+            h.set_batch(B)
+            h.profile(True)
+            h.round()
+            stats = h.profile_read()
+            h.profile(False)
+            assert "fwd1_block_gemm" in stats and ("gram" in stats) == (c["K1"] > 1), stats
+            if B > 32:
+                assert ("head_fused" if c["C"] <= 32 else "b1_step") in stats, stats
+            prob = replace(prob, B=B)
+            M.hieravg_round(prob, st)
+            assert np.array_equal(h.last_indices().astype(np.int64), st.last_indices)
+            ok, det = cases.parity_report(prob, h.params(), st.W)
+            assert ok, (B, det)
 
 
 @pytest.mark.parametrize("mode", ["delayed", "eager"])
