@@ -347,9 +347,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
   for (int s0 = 0; s0 < a.Kb; s0 += kSC) {
-    if (s0 > 0) load_stage(s0);
     store_stage();
     __syncthreads();
+    if (s0 + kSC < a.Kb) load_stage(s0 + kSC);  // in flight during the MFMAs
+    __builtin_amdgcn_sched_barrier(0);
     if (wave_on) {
 #pragma unroll
       for (int ss = 0; ss < kSC; ss += 2) {
@@ -396,11 +397,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
   }
 
-  if (nt == 0 && a.bias != nullptr && tid < kUM) {
-    const int m = mrow0 + tid;
-    if (m < a.Mrows) {
-      float sum = 0.0f;
-      for (int s = 0; s < a.Kb; ++s) sum += Gp[(int64_t)s * a.ldg + m];
+  if (nt == 0 && a.bias != nullptr) {  // four threads per unit, eight rows in flight each
+    __syncthreads();                   // the gradient tile has been read
+    const int u = tid & (kUM - 1), m = mrow0 + u;
+    float sum = 0.0f;
+#pragma unroll 8
+    for (int s = tid / kUM; s < a.Kb; s += 256 / kUM) sum += Gp[(int64_t)s * a.ldg + (m < a.Mrows ? m : 0)];
+    lds[tid] = sum;
+    __syncthreads();
+    if (tid < kUM && m < a.Mrows) {
+      sum = (lds[u] + lds[kUM + u]) + (lds[2 * kUM + u] + lds[3 * kUM + u]);
       float* bp = a.bias + (int64_t)p * a.w_pitch + m;
       const float b = *bp;
       float d = sum + a.wd * b;

@@ -235,15 +235,19 @@ __device__ inline uint32_t dpp_u(uint32_t v) {
 
 // Wo_g = base_g - lr_eff * sum_r G[r][:]^T X[r][:] (BlkArgs), workgroup tile
 // BM units x BN inputs of one group's block, contracted over the group's
-// R = K1*SG*B rows 16 at a time.  A lane loads one column of eight rows (a
-// wave instruction reads 64 consecutive columns of a row; the row's address
-// is scalar, from the row tables) and writes them as one 16-byte piece per
-// part: the transposition that the MFMA operands need costs nothing.
+// R = K1*SG*B rows 16 at a time.  A lane loads one or two columns of eight rows
+// (a wave instruction reads consecutive columns of a row, whose address is
+// scalar, from the row tables) and writes each column's eight values as one
+// 16-byte piece per part: the transposition that the MFMA operands need costs
+// nothing.  Two columns halve the load instructions, whose address processing
+// (16 cycles each for any width) kept the texture units 0.7 busy (512 x 3072, four
+// groups of 512 rows: 40.4 -> 37.8 us; with heavy-ball 53 -> 50).
 template <int BM, int BN, int WM, int WN, bool FULL, int WPE>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_waves_per_eu(WPE))) void k_block_update(
     BlkArgs a, const uint32_t* __restrict__ gtab, const uint32_t* __restrict__ xtab, int mtiles, int ntiles) {
   constexpr int NW = (BM / WM) * (BN / WN), NTH = 64 * NW;
-  constexpr int ROWS = BM + BN, UG = BM / 64, UX = BN / 64;  // 64-column groups of G and X
+  constexpr int VW = BM % 128 == 0 && BN % 128 == 0 ? 2 : 1;  // columns per lane
+  constexpr int ROWS = BM + BN, UC = 64 * VW, UG = BM / UC, UX = BN / UC;  // UC-column groups of G and X
   constexpr int UT = 2 * (UG + UX), NU = (UT + NW - 1) / NW;  // (row half, column group) units, per wave
   constexpr int MI = WM / 32, NI = WN / 32;
   static_assert(NW % 2 == 0, "a wave's units share their row half");
@@ -277,7 +281,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   // Unit u = wave + NW*i of a stage: row half u & 1, column group u >> 1
   // (the groups of G first).
   const int rh = wave & 1;
-  float v[NU][8];
+  float v[NU][8][VW];
   // Row offsets of the next stage to load, read (scalar) a stage ahead.
   uint32_t tg[8], tx[8];
   auto load_tab = [&](int s) {
@@ -296,7 +300,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
       const int cg = (wave + NW * i) >> 1;
       const bool isg = NW * i / 2 < UG && ((NW * (i + 1) - 1) / 2 < UG || cg < UG);
       const float* base = isg ? a.G : a.X;
-      const int col = isg ? mrow0 + 64 * cg : ncol0 + 64 * (cg - UG);
+      const int col = (isg ? mrow0 + UC * cg : ncol0 + UC * (cg - UG)) + VW * lane;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         // A row's range ends at its last column, and is empty for an error
@@ -304,7 +308,13 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
         const int bytes = isg ? (r0 + e < R ? 4 * a.Mrows : 0) : 4 * a.Ncols;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float*>(base) + ((uint64_t)(isg ? tg[e] : tx[e]) << 6), 0, bytes, 0x00020000);
-        v[i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4 * (col + lane), 0, 0));
+        if constexpr (VW == 2) {
+          const f32x2 x = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, 4 * col, 0, 0));
+          v[i][e][0] = x.x;
+          v[i][e][1] = x.y;
+        } else {
+          v[i][e][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4 * col, 0, 0));
+        }
       }
     }
     load_tab(s + 1);
@@ -349,19 +359,25 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
     gexp[i] = split_exp(e);
   }
   __syncthreads();
-  int ex[NU];
+  int ex[NU][VW];
 #pragma unroll
-  for (int i = 0; i < NU; ++i) {
-    const int cg = (wave + NW * i) >> 1;
-    ex[i] = cg < UG ? gexp[64 * cg + lane] : a.xexp;
-  }
+  for (int i = 0; i < NU; ++i)
+#pragma unroll
+    for (int x = 0; x < VW; ++x) {
+      const int cg = (wave + NW * i) >> 1;
+      ex[i][x] = cg < UG ? gexp[UC * cg + VW * lane + x] : a.xexp;
+    }
   auto store = [&](char* tile) {
 #pragma unroll
     for (int i = 0; i < NU; ++i) {
       if (NU * NW > UT && wave + NW * i >= UT) continue;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[i][e] = __builtin_amdgcn_ldexpf(v[i][e], ex[i]);
-      T::put8(tile, 64 * ((wave + NW * i) >> 1) + lane, rh, v[i]);
+      for (int x = 0; x < VW; ++x) {
+        float u[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = __builtin_amdgcn_ldexpf(v[i][e][x], ex[i][x]);
+        T::put8(tile, UC * ((wave + NW * i) >> 1) + VW * lane + x, rh, u);
+      }
     }
   };
 
@@ -444,14 +460,14 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   }
 }
 
-// Tiles of the block update: 128 x 256 in four waves (two workgroups per CU, so
-// one's ends run beside the other's MFMAs) where the grid holds four of them
-// per CU and more (1024 x 150528, four groups of 512 rows: 2.94 ms = 215
-// TFLOP/s; 256 x 256 in eight waves 2.99, 128 x 128 3.11, the float32 MFMA
-// form 5.16; the chip's power limit sets the clock there); else 128 x 128
-// (512 x 3072, four groups: 42 us against 57 with 64 x 64 tiles, 66 in
+// Tiles of the block update: 256 x 256 in eight waves where the grid holds two
+// of them per CU and more (1024 x 150528, four groups of 512 rows: 2.36 ms =
+// 268 TFLOP/s, as 128 x 256 in four waves; 128 x 128 2.6, the float32 MFMA
+// form 4.8; the chip's power limit sets the clock there); else 128 x 128
+// (512 x 3072, four groups: 38 us against 57 with 64 x 64 tiles, 66 in
 // float32) down to 256 workgroups, and 64 x 64 for smaller blocks (320 x 1024,
-// two groups of 243 rows: 11 us against 19, 14.6 in float32).
+// two groups of 243 rows: 11 us against 19, 14.6 in float32; 512 x 3072, two
+// groups of 2048 rows: 99 us against 115).
 void launch_block_update(hipStream_t s, const BlkArgs& a) {
   const int groups = a.P / a.SG;
   auto tiles = [&](int bm, int bn) { return (int64_t)groups * ((a.Mrows + bm - 1) / bm) * ((a.Ncols + bn - 1) / bn); };
@@ -465,8 +481,8 @@ void launch_block_update(hipStream_t s, const BlkArgs& a) {
     else                                                                                                       \
       launch(k_block_update<BM_, BN_, WM_, WN_, false, WPE_>, grid, th, 0, s, a, a.gtab, a.xtab, mt, nt);      \
   } while (0)
-  if (tiles(128, 256) >= 1024)
-    HAV_BU(128, 256, 128, 64, 2);
+  if (tiles(256, 256) >= 512)
+    HAV_BU(256, 256, 128, 64, 2);
   else if (tiles(128, 128) >= 256)
     HAV_BU(128, 128, 64, 64, 3);
   else

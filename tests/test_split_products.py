@@ -33,7 +33,7 @@ TILES = {
     "delayed_ragged": (cases.case("mlp", 12, 3, 3, 2, B=27, IN=333, H=300, C=37, N=300, sigma=0.5, lr=0.05, seed=206),
                        "delayed"),
     # 256 x 256 forward tiles (16 groups of 256 rows, 1024 units, 4 splits of
-    # 1024 features); the block update in 128 x 256 tiles
+    # 1024 features)
     "delayed_256": (cases.case("mlp", 32, 2, 8, 1, B=16, IN=4096, H=1024, C=5, N=300, sigma=0.5, lr=0.05, seed=207),
                     "delayed"),
     # 128 x 128 block-update tiles, ragged (320 units, 3008 features)
