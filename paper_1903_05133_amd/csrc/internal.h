@@ -270,8 +270,18 @@ void plan_split(int groups, int GM, int N, int K, int* KS, int* cps);
 // Outputs of 64 columns and more run as split products in 128- or 256-column
 // tiles (k_split.hip), narrower ones (the logits of few classes) as 16-column
 // float32 MFMA blocks (k_gemm.hip): there a wide tile is mostly padding (4 x 16
-// rows of 16 columns over 3072 features take 5.6 us).
-inline bool fwd_split_takes(int N) { return N >= 64; }
+// rows of 16 columns over 3072 features take 5.6 us).  So do groups of up to 32
+// rows whose weights (`groups` blocks of N x K) stream from HBM: the blocks
+// read 256 consecutive bytes of a weight row at a time, the split tiles 64, and
+// the few rows leave nothing else to do.  The line for 32 rows is the 256 MB of
+// the last-level cache (64 x 32 rows, 3072 features: 512 units 83 us against
+// 96 split, 192 units (151 MB) 38 against 33); for 16 rows, one MFMA block,
+// 64 MB (16 x 16 rows: 512 units (101 MB) 19.9 against 21.0, 192 units (38 MB)
+// 11.7 against 11.6, 128 units 9.6 against 7.7).
+inline bool fwd_split_takes(int groups, int GM, int N, int K) {
+  const int64_t wbytes = (int64_t)groups * N * K * 4;
+  return N >= 64 && (GM > 32 || wbytes <= ((int64_t)(GM > 16 ? 256 : 64) << 20));
+}
 void launch_fwd_nt(hipStream_t s, const FwdArgs& a, ASource src);
 void plan_split_nt(int groups, int GM, int N, int K, int* KS, int* cps);
 

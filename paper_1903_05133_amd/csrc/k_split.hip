@@ -159,12 +159,14 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
 //    with 128 x 128 tiles; the float32 MFMA form took 66);
 //  - fewer rows per group: 128 x 128 (8 x 128 rows: 25.5 us against 28.4; 58
 //    in float32), 64 x 128 (8 x 64 rows: 20 us against 21.6 with 128 rows;
-//    29 in float32), 32 x 128.
+//    29 in float32), 32 x 128 (four workgroups per CU: 64 x 32 rows against 192
+//    units over 3072 features 33.3 us, two per CU 38.6, 38.1 in float32; at 64
+//    rows two are faster, 28.4 us against 33.0 for 64 x 64 rows, 128 units).
 enum FwdTile { FT_256, FT_128x256, FT_128, FT_64, FT_32 };
 struct FwdTileShape {
   int bm, bn, wgs;  // rows, columns, workgroups a launch aims for
 };
-static constexpr FwdTileShape kFwdTiles[] = {{256, 256, 256}, {128, 256, 256}, {128, 128, 256}, {64, 128, 512}, {32, 128, 512}};
+static constexpr FwdTileShape kFwdTiles[] = {{256, 256, 256}, {128, 256, 256}, {128, 128, 256}, {64, 128, 512}, {32, 128, 1024}};
 static int64_t fwd_tiles(FwdTile t, int64_t groups, int GM, int N) {
   return groups * ((GM + kFwdTiles[t].bm - 1) / kFwdTiles[t].bm) * ((N + kFwdTiles[t].bn - 1) / kFwdTiles[t].bn);
 }
@@ -179,7 +181,7 @@ static FwdTile fwd_tile(int64_t groups, int GM, int N, int K) {
 
 void plan_split(int groups, int GM, int N, int K, int* KS, int* cps) {
   const int nch = K / kKC;
-  if (!fwd_split_takes(N)) {
+  if (!fwd_split_takes(groups, GM, N, K)) {
     plan_split_nt(groups, GM, N, K, KS, cps);
     return;
   }
@@ -192,12 +194,12 @@ void plan_split(int groups, int GM, int N, int K, int* KS, int* cps) {
 }
 
 void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
-  if (!fwd_split_takes(a.N)) {
+  const int GM = a.SG * a.Mp;
+  const int groups = a.vS > 0 ? a.P / a.vS : a.P / a.SG;
+  if (!fwd_split_takes(groups, GM, a.N, a.K)) {
     launch_fwd_nt(s, a, src);
     return;
   }
-  const int GM = a.SG * a.Mp;
-  const int groups = a.vS > 0 ? a.P / a.vS : a.P / a.SG;
 #define HAV_FS1(BM_, BN_, WM_, WN_, WPE_, NPART_, SRC_, FULL_)                                                  \
   launch(k_fwd_split<BM_, BN_, WM_, WN_, NPART_, SRC_, FULL_, WPE_>,                                            \
          (unsigned)((int64_t)groups * a.KS * ((GM + BM_ - 1) / BM_) * ((a.N + BN_ - 1) / BN_)),                 \

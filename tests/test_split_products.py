@@ -26,6 +26,10 @@ TILES = {
     "rows_48": (cases.case("mlp", 4, 2, 2, 1, B=33, IN=190, H=130, C=70, N=90, lr=0.05, seed=202), "eager"),
     "rows_80": (cases.case("mlp", 2, 2, 2, 1, B=65, IN=320, H=100, C=130, N=90, lr=0.05, seed=203), "eager"),
     "rows_160": (cases.case("mlp", 2, 1, 1, 2, B=150, IN=129, H=192, C=33, N=90, lr=0.05, seed=204), "eager"),
+    # few rows over weights beyond the cache (71 MB for 16 rows, 273 MB for 32):
+    # float32 16-column blocks, ragged in rows and units
+    "stream_16": (cases.case("mlp", 16, 4, 1, 2, B=13, IN=4090, H=270, C=20, N=90, lr=0.05, seed=225), "eager"),
+    "stream_32": (cases.case("mlp", 16, 2, 1, 1, B=23, IN=4090, H=1035, C=20, N=90, lr=0.05, seed=226), "eager"),
     # 128 x 256 tiles, full and ragged in rows, units and features; the block
     # update in 64 x 64 tiles
     "delayed_full": (cases.case("mlp", 16, 4, 4, 2, B=32, IN=512, H=256, C=7, N=300, sigma=0.5, lr=0.05, seed=205),
