@@ -268,7 +268,7 @@ void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src);
 // split.
 void plan_split(int groups, int GM, int N, int K, int* KS, int* cps);
 // Outputs of 64 columns and more run as split products in 128- or 256-column
-// tiles (k_split.hip), narrower ones (the logits of few classes) as 16-column
+// tiles (k_delayed.hip), narrower ones (the logits of few classes) as 16-column
 // float32 MFMA blocks (k_gemm.hip): there a wide tile is mostly padding (4 x 16
 // rows of 16 columns over 3072 features take 5.6 us).  So do groups of up to 32
 // rows whose weights (`groups` blocks of N x K) stream from HBM: the blocks

@@ -1,4 +1,5 @@
-// Kernels of the delayed first-layer update (include/hieravg.h,
+// The wide contractions of a round as split float32 products (split.h), and
+// the kernels of the delayed first-layer update (include/hieravg.h,
 // HIERAVG_UPDATE_DELAYED): within a block of K1 local steps (Algorithm 1,
 // Sec. 3.1) every learner of a cluster starts from the same first weight
 // block Wb, and after k steps its block is Wb - lr * sum_{k'<k} G_k'^T X_k'.
@@ -6,14 +7,18 @@
 // k_gram:         the Gram blocks X_k X_k'^T (k' < k) of each learner's
 //                 minibatches in each block, which turn the forward from Wb
 //                 into the forward from the learner's current block.
-// (The block's forward and block-end update are in k_split.hip.)
+// k_fwd_split:    part[ks][p][m][n] = sum_{k in split ks} A_p[m][k] * W_p[n][k]
+//                 (the forward of either layer; the layouts of FwdArgs).
+// k_block_update: the block-end update of the delayed schedule, one GEMM per
+//                 cluster (BlkArgs).
+// k_gram_split:   the Gram blocks of minibatches of more than 32 samples.
 #include <algorithm>
 
-#include "internal.h"
+#include "split.h"
 
 namespace hav {
 
-constexpr int kKC = 64;  // K floats per LDS chunk
+constexpr int kKC = 64;  // K floats per LDS chunk (k_gram) and per chunk of a split
 
 // ------------------------------------------------------------ Gram blocks
 // One workgroup per (learner p, block b, K split ks): all step pairs k2 < k of
@@ -203,6 +208,587 @@ void launch_gram_reduce(hipStream_t s, float* gram, int P, int K1, int K2, int B
   const int64_t n4 = (int64_t)K2 * P * pairs * blk4;
   const int64_t g = std::min<int64_t>((n4 + 255) / 256, 2048);
   launch(k_gram_reduce, (unsigned)g, 256, 0, s, gram, split, n4, K1, pairs, blk4, KSG);
+}
+
+// ------------------------------------------------------------ forward
+// Workgroup tile BM rows (samples) x BN columns (units), one K split; wave
+// tile WM x WN.  The tile's rows of both operands are read 16 k at a time
+// with 16-byte loads (four lanes per row), one stage ahead in registers, and
+// go to LDS as bf16 parts (two buffers, one barrier per stage).  FULL: every
+// row and column in range.
+template <int BM, int BN, int WM, int WN, int NPART, int ASRC, bool FULL, int WPE>
+__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_waves_per_eu(WPE))) void k_fwd_split(
+    FwdArgs a, int ntiles, int mtiles) {
+  constexpr int NTH = 64 * (BM / WM) * (BN / WN);
+  constexpr int ROWS = BM + BN, RPP = NTH / 4, NP = (ROWS + RPP - 1) / RPP;  // pieces per thread, rows per pass
+  constexpr int MI = WM / 32, NI = WN / 32;
+  using T = SplitTile<ROWS, NPART>;
+  __shared__ __attribute__((aligned(16))) char lds[NTH == 512 ? 3 : 2][T::kBytes];
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  const int q1 = qdiv_small(bid, ntiles, qdiv_inv(ntiles)), nt = bid - q1 * ntiles;
+  const int q2 = qdiv_small(q1, mtiles, qdiv_inv(mtiles)), mt = q1 - q2 * mtiles;
+  const int g = qdiv_small(q2, a.KS, qdiv_inv(a.KS)), ks = q2 - g * a.KS;
+  const int GM = a.SG * a.Mp;
+  const int nch = a.K / kKC;
+  const int c0 = ks * a.cps, c1 = min(nch, c0 + a.cps);
+  const int ns = 4 * (c1 - c0);  // stages
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int wm = wave / (BN / WN) * WM, wn = wave % (BN / WN) * WN;
+  const int mbase = mt * BM, nbase = nt * BN;
+  const int sr = tid >> 2, sq = tid & 3;
+
+  // Whether this thread's row of pass i is one of A's (the same for a wave).
+  auto is_a = [&](int i) { return RPP * (i + 1) <= BM || (RPP * i < BM && sr + RPP * i < BM); };
+  auto none = [&](int i) { return RPP * (i + 1) > ROWS && sr + RPP * i >= ROWS; };  // no row for this thread
+  const float* src[NP];
+  bool ok[NP];
+  int ex[NP];  // two parts: the row's power-of-two scale
+  const float* wp = a.W + (int64_t)(g / a.wdiv) * a.w_pitch;
+  const uint32_t* wmax = NPART == 2 ? a.wmax + (int64_t)(g / a.wdiv) * a.wmax_pitch : nullptr;
+  const float inv_mp = qdiv_inv(a.Mp), inv_vs = qdiv_inv(a.vS > 0 ? a.vS : 1);
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    if (none(i)) continue;
+    const int r = sr + RPP * i;
+    if (is_a(i)) {
+      const int m = mbase + r;
+      const int jj = qdiv_small(m, a.Mp, inv_mp), sm = m - jj * a.Mp;
+      ok[i] = FULL || (m < GM && sm < a.M);
+      const int v = ok[i] ? jj : 0;
+      int64_t p = (int64_t)g * a.SG + v;
+      if (a.vS > 0) {
+        const int k = qdiv_small(v, a.vS, inv_vs);
+        p = (int64_t)k * a.P + (int64_t)g * a.vS + (v - k * a.vS);
+      }
+      const int sc = ok[i] ? sm : 0;
+      const int64_t row = ASRC == A_GATHER ? (int64_t)a.idx[p * a.M + sc] : p * a.Mp + sc;
+      src[i] = a.A + row * a.lda + 4 * sq;
+      ex[i] = a.xexp;
+    } else {
+      const int n = nbase + r - BM;
+      ok[i] = true;  // columns past N repeat row 0 and are not stored
+      const int nc = FULL || n < a.N ? n : 0;
+      src[i] = wp + (int64_t)nc * a.ldw + 4 * sq;
+      if (NPART == 2) ex[i] = split_exp(wmax[nc]);
+    }
+    src[i] += (int64_t)c0 * kKC;
+  }
+  f32x4 v[NP];
+  auto load = [&](int s) {  // past the end: the last stage again, unused
+    const int o = 16 * min(s, ns - 1);
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      if (!none(i)) v[i] = *(const f32x4*)(src[i] + o);
+  };
+  auto store = [&](char* tile) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      if (none(i)) continue;
+      f32x4 x = v[i];
+      if (is_a(i)) {
+        if (!FULL && !ok[i]) x = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (ASRC == A_RELU) {  // NaN stays NaN
+          x.x = x.x < 0.0f ? 0.0f : x.x;
+          x.y = x.y < 0.0f ? 0.0f : x.y;
+          x.z = x.z < 0.0f ? 0.0f : x.z;
+          x.w = x.w < 0.0f ? 0.0f : x.w;
+        }
+      }
+      if (NPART == 2) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_ldexpf(x[e], ex[i]);
+      }
+      T::put4(tile, sr + RPP * i, sq, x);
+    }
+  };
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  if constexpr (NTH == 512)
+    split_loop8<ROWS, NPART, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
+  else
+    split_loop4<ROWS, NPART, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
+
+  int en[NI];  // two parts: minus the scales of the lane's columns
+#pragma unroll
+  for (int j = 0; j < NI; ++j)
+    en[j] = NPART == 2 ? -a.xexp - split_exp(wmax[min(nbase + wn + 32 * j + l32, a.N - 1)]) : 0;
+  const int64_t PT = a.PT > 0 ? a.PT : a.P;
+  const int64_t gbase = a.vS > 0 ? (int64_t)g * a.vS : (int64_t)g * a.SG;
+  const int64_t kstride = a.vS > 0 ? a.P : 0;
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    // The lane's rows 8t + e (e < 4) share one member (Mp is a multiple of 16).
+    const int mrow = mbase + wm + 32 * i + 4 * lhi;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int row = mrow + 8 * t;
+      if (!FULL && row >= GM) continue;
+      const int mv = qdiv_small(row, a.Mp, inv_mp), sm = row - mv * a.Mp;
+      const int vk = a.vS > 0 ? qdiv_small(mv, a.vS, inv_vs) : 0, vj = a.vS > 0 ? mv - vk * a.vS : mv;
+      float* dst = a.part + (((int64_t)ks * PT + vk * kstride + gbase + vj) * a.Mp + sm) * a.N + nbase + wn + l32;
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        if (!FULL && nbase + wn + 32 * j + l32 >= a.N) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) 
+          dst[(int64_t)e * a.N + 32 * j] =
+              NPART == 2 ? __builtin_amdgcn_ldexpf(acc[i][j][4 * t + e], en[j]) : acc[i][j][4 * t + e];
+      }
+    }
+  }
+}
+
+// The tile of a forward over `groups` row groups of GM rows each.
+//  - 256 x 256 where the operands are long: with the split count that brings
+//    the grid to one workgroup per CU, 1024 k and more per split (a 512-row
+//    group against 1024 units over 150528 features: 2.24 ms = 282 TFLOP/s, with
+//    128 x 256 tiles 2.47; over 3072 features the 128 x 256 tile is as fast
+//    with half the splits);
+//  - 128 x 256 where at least 32 such tiles exist, so that 8 splits fill the
+//    GPU (2048 rows, 512 units, 3072 features in two parts: 28.6 us, 31.8 us
+//    with 128 x 128 tiles; the float32 MFMA form took 66);
+//  - fewer rows per group: 128 x 128 (8 x 128 rows: 25.5 us against 28.4; 58
+//    in float32), 64 x 128 (8 x 64 rows: 20 us against 21.6 with 128 rows;
+//    29 in float32), 32 x 128 (four workgroups per CU: 64 x 32 rows against 192
+//    units over 3072 features 33.3 us, two per CU 38.6, 38.1 in float32; at 64
+//    rows two are faster, 28.4 us against 33.0 for 64 x 64 rows, 128 units).
+enum FwdTile { FT_256, FT_128x256, FT_128, FT_64, FT_32 };
+struct FwdTileShape {
+  int bm, bn, wgs;  // rows, columns, workgroups a launch aims for
+};
+static constexpr FwdTileShape kFwdTiles[] = {{256, 256, 256}, {128, 256, 256}, {128, 128, 256}, {64, 128, 512}, {32, 128, 1024}};
+static int64_t fwd_tiles(FwdTile t, int64_t groups, int GM, int N) {
+  return groups * ((GM + kFwdTiles[t].bm - 1) / kFwdTiles[t].bm) * ((N + kFwdTiles[t].bn - 1) / kFwdTiles[t].bn);
+}
+static FwdTile fwd_tile(int64_t groups, int GM, int N, int K) {
+  if (GM % 256 == 0 && N % 256 == 0) {
+    const int64_t ks = (256 + fwd_tiles(FT_256, groups, GM, N) - 1) / fwd_tiles(FT_256, groups, GM, N);
+    if (K / ks >= 1024) return FT_256;
+  }
+  if (GM > 64) return N > 128 && fwd_tiles(FT_128x256, groups, GM, N) >= 32 ? FT_128x256 : FT_128;
+  return GM > 32 ? FT_64 : FT_32;
+}
+
+void plan_split(int groups, int GM, int N, int K, int* KS, int* cps) {
+  const int nch = K / kKC;
+  if (!fwd_split_takes(groups, GM, N, K)) {
+    plan_split_nt(groups, GM, N, K, KS, cps);
+    return;
+  }
+  const FwdTile t = fwd_tile(groups, GM, N, K);
+  const int64_t tiles = fwd_tiles(t, groups, GM, N);
+  int ks = (int)std::min<int64_t>(nch, std::max<int64_t>(1, (kFwdTiles[t].wgs + tiles - 1) / tiles));
+  const int c = (nch + ks - 1) / ks;
+  *KS = (nch + c - 1) / c;
+  *cps = c;
+}
+
+void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
+  const int GM = a.SG * a.Mp;
+  const int groups = a.vS > 0 ? a.P / a.vS : a.P / a.SG;
+  if (!fwd_split_takes(groups, GM, a.N, a.K)) {
+    launch_fwd_nt(s, a, src);
+    return;
+  }
+#define HAV_FS1(BM_, BN_, WM_, WN_, WPE_, NPART_, SRC_, FULL_)                                                  \
+  launch(k_fwd_split<BM_, BN_, WM_, WN_, NPART_, SRC_, FULL_, WPE_>,                                            \
+         (unsigned)((int64_t)groups * a.KS * ((GM + BM_ - 1) / BM_) * ((a.N + BN_ - 1) / BN_)),                 \
+         64 * (BM_ / WM_) * (BN_ / WN_), 0, s, a, (a.N + BN_ - 1) / BN_, (GM + BM_ - 1) / BM_)
+#define HAV_FS(BM_, BN_, WM_, WN_, WPE_)                                                                        \
+  do {                                                                                                          \
+    const bool full = GM % BM_ == 0 && a.N % BN_ == 0 && a.M == a.Mp;                                           \
+    if (src == A_RELU)                                                                                          \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_RELU, false);                                                      \
+    else if (a.wmax && full)                                                                                    \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 2, A_GATHER, true);                                                     \
+    else if (a.wmax)                                                                                            \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 2, A_GATHER, false);                                                    \
+    else if (full)                                                                                              \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_GATHER, true);                                                     \
+    else                                                                                                        \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_GATHER, false);                                                    \
+  } while (0)
+  switch (fwd_tile(groups, GM, a.N, a.K)) {
+    case FT_256: HAV_FS(256, 256, 128, 64, 2); break;
+    case FT_128x256: HAV_FS(128, 256, 64, 64, 2); break;
+    case FT_128: HAV_FS(128, 128, 64, 32, 2); break;
+    case FT_64: HAV_FS(64, 128, 64, 32, 4); break;
+    default: HAV_FS(32, 128, 32, 32, 4); break;
+  }
+#undef HAV_FS
+#undef HAV_FS1
+}
+
+// ------------------------------------------------------------ block update
+template <int CTRL>
+__device__ inline uint32_t dpp_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+// Wo_g = base_g - lr_eff * sum_r G[r][:]^T X[r][:] (BlkArgs), workgroup tile
+// BM units x BN inputs of one group's block, contracted over the group's
+// R = K1*SG*B rows 16 at a time.  A lane loads one or two columns of eight rows
+// (a wave instruction reads consecutive columns of a row, whose address is
+// scalar, from the row tables) and writes each column's eight values as one
+// 16-byte piece per part: the transposition that the MFMA operands need costs
+// nothing.  Two columns halve the load instructions, whose address processing
+// (16 cycles each for any width) kept the texture units 0.7 busy (512 x 3072, four
+// groups of 512 rows: 40.4 -> 37.8 us; with heavy-ball 53 -> 50).
+template <int BM, int BN, int WM, int WN, bool FULL, int WPE>
+__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_waves_per_eu(WPE))) void k_block_update(
+    BlkArgs a, const uint32_t* __restrict__ gtab, const uint32_t* __restrict__ xtab, int mtiles, int ntiles) {
+  constexpr int NW = (BM / WM) * (BN / WN), NTH = 64 * NW;
+  constexpr int VW = BM % 128 == 0 && BN % 128 == 0 ? 2 : 1;  // columns per lane
+  constexpr int ROWS = BM + BN, UC = 64 * VW, UG = BM / UC, UX = BN / UC;  // UC-column groups of G and X
+  constexpr int UT = 2 * (UG + UX), NU = (UT + NW - 1) / NW;  // (row half, column group) units, per wave
+  constexpr int MI = WM / 32, NI = WN / 32;
+  static_assert(NW % 2 == 0, "a wave's units share their row half");
+  using T = SplitTile<ROWS, 2>;
+  __shared__ int gexp[BM];  // the scales of the tile's units
+  __shared__ __attribute__((aligned(16))) char lds[NTH == 512 ? 3 : 2][T::kBytes];
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  const int mt = bid % mtiles;
+  const int nt = (bid / mtiles) % ntiles;
+  const int g = bid / (ntiles * mtiles);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int mrow0 = mt * BM, ncol0 = nt * BN;
+  const int wm = wave / (BN / WN) * WM, wn = wave % (BN / WN) * WN;
+  const int R = a.K1 * a.SG * a.B;
+  const int Rp = (R + 31) / 32 * 32, ns = Rp / 16;  // even
+  const uint32_t* gt = gtab + (int64_t)g * Rp;
+  const uint32_t* xt = xtab + (int64_t)g * Rp;
+  if (a.tail && mt == 0) {
+    f32x4* Tl = (f32x4*)a.tail + (int64_t)g * a.SG * (a.tail_pitch / 4);
+    const int64_t p4 = a.tail_pitch / 4, n4 = a.tail_len / 4, per = (n4 + ntiles - 1) / ntiles;
+    const int64_t i1 = min(n4, (nt + 1) * per);
+    for (int64_t i = nt * per + tid; i < i1; i += NTH) {
+      f32x4 sum = Tl[i];
+      for (int j = 1; j < a.SG; ++j) sum += Tl[j * p4 + i];
+      const f32x4 mean = sum / (float)a.SG;
+      for (int j = 0; j < a.SG; ++j) Tl[j * p4 + i] = mean;
+    }
+  }
+  // Unit u = wave + NW*i of a stage: row half u & 1, column group u >> 1
+  // (the groups of G first).
+  const int rh = wave & 1;
+  float v[NU][8][VW];
+  // Row offsets of the next stage to load, read (scalar) a stage ahead.
+  uint32_t tg[8], tx[8];
+  auto load_tab = [&](int s) {
+    const int r0 = 16 * min(s, ns - 1) + 8 * rh;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      tg[e] = gt[r0 + e];
+      tx[e] = xt[r0 + e];
+    }
+  };
+  auto load = [&](int s) {
+    const int r0 = 16 * min(s, ns - 1) + 8 * rh;  // past the end: the last stage again, unused
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      if (NU * NW > UT && wave + NW * i >= UT) continue;
+      const int cg = (wave + NW * i) >> 1;
+      const bool isg = NW * i / 2 < UG && ((NW * (i + 1) - 1) / 2 < UG || cg < UG);
+      const float* base = isg ? a.G : a.X;
+      const int col = (isg ? mrow0 + UC * cg : ncol0 + UC * (cg - UG)) + VW * lane;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        // A row's range ends at its last column, and is empty for an error
+        // row past the contraction: what lies outside reads 0.
+        const int bytes = isg ? (r0 + e < R ? 4 * a.Mrows : 0) : 4 * a.Ncols;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(base) + ((uint64_t)(isg ? tg[e] : tx[e]) << 6), 0, bytes, 0x00020000);
+        if constexpr (VW == 2) {
+          const f32x2 x = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, 4 * col, 0, 0));
+          v[i][e][0] = x.x;
+          v[i][e][1] = x.y;
+        } else {
+          v[i][e][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4 * col, 0, 0));
+        }
+      }
+    }
+    load_tab(s + 1);
+  };
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  load_tab(0);
+  const int voff = 4 * (4 * lhi * (int)a.ldw + l32), ld4 = 4 * (int)a.ldw;
+  const float* Wb = a.Wb + (int64_t)(g / a.base_div) * a.nbase * a.wb_pitch;
+  // Blocks of 32 rows and of 32 columns are whole (both sizes are multiples of 64).
+  auto in = [&](int b) {
+    return FULL || (mrow0 + wm + 32 * (b / NI) < a.Mrows && ncol0 + wn + 32 * (b % NI) < a.Ncols);
+  };
+  auto rsrc = [&](const float* base, int b) {
+    return buf_rsrc(base + (int64_t)(mrow0 + wm + 32 * (b / NI)) * a.ldw + ncol0 + wn, 32ull * (uint64_t)a.ldw * 4);
+  };
+  auto soff = [&](int b, int r) { return (8 * (r >> 2) + (r & 3)) * ld4 + 128 * (b % NI); };
+  auto ld = [&](const float* base, int b, float (&u)[16]) {
+    if (!in(b)) return;
+    const __amdgpu_buffer_rsrc_t rs = rsrc(base, b);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      u[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff(b, r), 0));
+  };
+  constexpr int NB = MI * NI, NQ = NB < 3 ? NB : 3;  // blocks, and those in flight
+  float w[NQ][16];
+  for (int i = tid; i < BM; i += NTH) {
+    const int m = min(mrow0 + i, a.Mrows - 1);
+    uint32_t e = 0;
+    for (int c = 0; c < a.gm_n; ++c) e = max(e, a.gmax[((int64_t)(g / a.gm_div) * a.gm_n + c) * a.Mrows + m]);
+    if (a.hb) {  // the errors carry their step's coefficient
+      float f = 0.0f;
+      for (int k = 0; k < a.K1; ++k) f = fmaxf(f, fabsf(a.hb[a.hb_g + k]));
+      e = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, e) * f);
+    }
+    gexp[i] = split_exp(e);
+  }
+  __syncthreads();
+  int ex[NU][VW];
+#pragma unroll
+  for (int i = 0; i < NU; ++i)
+#pragma unroll
+    for (int x = 0; x < VW; ++x) {
+      const int cg = (wave + NW * i) >> 1;
+      ex[i][x] = cg < UG ? gexp[UC * cg + VW * lane + x] : a.xexp;
+    }
+  auto store = [&](char* tile) {
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      if (NU * NW > UT && wave + NW * i >= UT) continue;
+#pragma unroll
+      for (int x = 0; x < VW; ++x) {
+        float u[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = __builtin_amdgcn_ldexpf(v[i][e][x], ex[i][x]);
+        T::put8(tile, UC * ((wave + NW * i) >> 1) + VW * lane + x, rh, u);
+      }
+    }
+  };
+
+  if constexpr (NTH == 512)
+    split_loop8<ROWS, 2, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
+  else
+    split_loop4<ROWS, 2, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
+
+  // Straight from the accumulators: lane (l, h) holds column l of rows
+  // 8t + 4h + e of each 32 x 32 block, so an instruction reads or writes two
+  // 128-byte row segments.  Buffer accesses: one lane offset for the whole
+  // tile, scalar offsets for the rows; the base of the blocks ahead is in
+  // flight.
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int b = 0; b < NQ; ++b) ld(Wb, b, w[b]);
+  const float c1 = a.hb ? a.hb[a.hb_c1] : 1.0f, c2 = a.hb ? a.hb[a.hb_c2] : 0.0f;
+  const float c3 = a.hb ? 1.0f / a.lr_div : -(*a.lr / a.lr_div);
+  uint32_t mx[16];  // magnitudes as bits: NaN and infinity are the largest
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int i = b / NI, j = b % NI;
+    float (&x)[16] = w[b % NQ];
+    if (in(b)) {
+      float u[16];
+      if (a.nbase > 1) {  // the mean of the bases, added in order
+        for (int c = 1; c < a.nbase; ++c) {
+          ld(Wb + (int64_t)c * a.wb_pitch, b, u);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) x[r] += u[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[r] = x[r] / (float)a.nbase;
+      }
+      if (a.hb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[r] *= c1;
+        if (a.B2) {
+          const float* b2 = a.B2 + (int64_t)g * a.b2_rows * a.b2_pitch;
+          float bm[16];
+          ld(b2, b, bm);
+          for (int c = 1; c < a.b2_rows; ++c) {
+            ld(b2 + (int64_t)c * a.b2_pitch, b, u);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) bm[r] += u[r];
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) x[r] += c2 * (bm[r] / (float)a.b2_rows);
+        }
+      }
+      const __amdgpu_buffer_rsrc_t rs = rsrc(a.Wo + (int64_t)g * a.wo_pitch, b);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int er = -a.xexp - gexp[wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3)];  // minus the scales
+        x[r] += c3 * __builtin_amdgcn_ldexpf(acc[i][j][r], er);
+        const uint32_t m = __builtin_bit_cast(uint32_t, x[r]) & 0x7fffffffu;
+        mx[r] = j == 0 ? m : max(mx[r], m);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[r]), rs, voff, soff(b, r), 0);
+      }
+    }
+    if (b + NQ < NB) ld(Wb, b + NQ, x);
+    if (j == NI - 1 && a.wmax_out && in(b - j)) {
+      // Row maxima over the wave's columns: over 16 lanes by DPP moves, then
+      // lane l takes row l % 16 of its half.  Only a value above what the
+      // table holds goes out (a few per row in a launch).
+      uint32_t mine = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        uint32_t m = mx[r];
+        m = max(m, dpp_u<0xB1>(m));  // lanes i^1, i^2, 7-i, 15-i
+        m = max(m, dpp_u<0x4E>(m));
+        m = max(m, dpp_u<0x141>(m));
+        m = max(m, dpp_u<0x140>(m));
+        if ((lane & 15) == r) mine = m;
+      }
+      const int r = lane & 15;
+      uint32_t* d = a.wmax_out + (int64_t)g * a.Mrows + mrow0 + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3);
+      if (mine > __hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(d, mine);
+    }
+  }
+}
+
+// Tiles of the block update: 256 x 256 in eight waves where the grid holds two
+// of them per CU and more (1024 x 150528, four groups of 512 rows: 2.36 ms =
+// 268 TFLOP/s, as 128 x 256 in four waves; 128 x 128 2.6, the float32 MFMA
+// form 4.8; the chip's power limit sets the clock there); else 128 x 128
+// (512 x 3072, four groups: 38 us against 57 with 64 x 64 tiles, 66 in
+// float32) down to 256 workgroups, and 64 x 64 for smaller blocks (320 x 1024,
+// two groups of 243 rows: 11 us against 19, 14.6 in float32; 512 x 3072, two
+// groups of 2048 rows: 99 us against 115).
+void launch_block_update(hipStream_t s, const BlkArgs& a) {
+  const int groups = a.P / a.SG;
+  auto tiles = [&](int bm, int bn) { return (int64_t)groups * ((a.Mrows + bm - 1) / bm) * ((a.Ncols + bn - 1) / bn); };
+#define HAV_BU(BM_, BN_, WM_, WN_, WPE_)                                                                       \
+  do {                                                                                                         \
+    const int mt = (a.Mrows + BM_ - 1) / BM_, nt = (a.Ncols + BN_ - 1) / BN_;                                  \
+    const unsigned grid = (unsigned)((int64_t)groups * mt * nt);                                               \
+    constexpr int th = 64 * (BM_ / WM_) * (BN_ / WN_);                                                         \
+    if (a.Mrows % BM_ == 0 && a.Ncols % BN_ == 0)                                                              \
+      launch(k_block_update<BM_, BN_, WM_, WN_, true, WPE_>, grid, th, 0, s, a, a.gtab, a.xtab, mt, nt);       \
+    else                                                                                                       \
+      launch(k_block_update<BM_, BN_, WM_, WN_, false, WPE_>, grid, th, 0, s, a, a.gtab, a.xtab, mt, nt);      \
+  } while (0)
+  if (tiles(256, 256) >= 512)
+    HAV_BU(256, 256, 128, 64, 2);
+  else if (tiles(128, 128) >= 256)
+    HAV_BU(128, 128, 64, 64, 3);
+  else
+    HAV_BU(64, 64, 32, 32, 4);
+#undef HAV_BU
+}
+
+// ------------------------------------------------------------ Gram blocks past 32 samples
+// gram[ks][b][p][k][k2][s][s2] = X[idx_(b,k,p,s)] . X[idx_(b,k2,p,s2)] over
+// feature split ks for k2 < k (rows and columns past B zero): per learner and
+// block, the 128 x 128 tiles of the rows' Gram matrix (row k*Bp + s) that hold
+// such a pair, as two f16 parts of the rows (their magnitude is known).
+// 64 learners, 4 blocks of 8 x 64 samples of 3072 features: 0.86 ms.
+constexpr int kGB = 128;
+__host__ __device__ inline bool gram_tile(int R, int Bp, int mt, int nt) {
+  return (min(R, kGB * (mt + 1)) - 1) / Bp > kGB * nt / Bp;
+}
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_gram_split(
+    const float* __restrict__ X, int64_t ldx, int K, const int32_t* __restrict__ idx, float* __restrict__ gram, int P,
+    int K1, int K2, int B, int Bp, int KSG, int cps, int ntiles, int xexp) {
+  constexpr int ROWS = 2 * kGB, RPP = 128, NP = ROWS / RPP, MI = 2;
+  using T = SplitTile<ROWS, 2>;
+  __shared__ __attribute__((aligned(16))) char lds[3][T::kBytes];
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  int t = bid % ntiles;
+  const int ks = bid / ntiles % KSG;
+  const int pb = bid / (ntiles * KSG), p = pb % P, b = pb / P;
+  const int R = K1 * Bp;
+  int mt = 0, nt = 0;
+  for (;; ) {  // the t-th tile that holds a pair
+    if (gram_tile(R, Bp, mt, nt) && t-- == 0) break;
+    if (++nt > mt) {
+      nt = 0;
+      ++mt;
+    }
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int wm = (wave >> 2) * 64, wn = (wave & 3) * 32;
+  const int c0 = ks * cps, c1 = min(K / kKC, c0 + cps), ns = 4 * (c1 - c0);
+  const int sr = tid >> 2, sq = tid & 3;
+  const float* src[NP];
+  bool ok[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int r = (i == 0 ? mt : nt) * kGB + sr, k = min(r, R - 1) / Bp, s = min(r, R - 1) - k * Bp;
+    ok[i] = r < R && s < B;
+    src[i] = X + (int64_t)idx[((int64_t)(b * K1 + k) * P + p) * B + (ok[i] ? s : 0)] * ldx + 4 * sq + (int64_t)c0 * kKC;
+  }
+  f32x4 v[NP];
+  auto load = [&](int s) {
+    const int o = 16 * min(s, ns - 1);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) v[i] = *(const f32x4*)(src[i] + o);
+  };
+  auto store = [&](char* tile) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      f32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = ok[i] ? __builtin_amdgcn_ldexpf(v[i][e], xexp) : 0.0f;
+      T::put4(tile, sr + RPP * i, sq, x);
+    }
+  };
+  f32x16 acc[MI][1];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.0f;
+  split_loop8<ROWS, 2, MI, 1>(lds[0], ns, wm, kGB + wn, l32, lhi, wave >> 2, acc, load, store);
+  const int n = nt * kGB + wn + l32, k2 = n / Bp, s2 = n - k2 * Bp;
+  float* out = gram + (((int64_t)ks * K2 + b) * P + p) * K1 * K1 * Bp * Bp;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = mt * kGB + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), k = m / Bp;
+      if (m < R && n < R && k2 < k)
+        out[((int64_t)(k * K1 + k2) * Bp + (m - k * Bp)) * Bp + s2] = __builtin_amdgcn_ldexpf(acc[i][0][r], -2 * xexp);
+    }
+}
+
+static int gram_tiles(int K1, int Bp) {
+  const int R = K1 * Bp, mts = (R + kGB - 1) / kGB;
+  int n = 0;
+  for (int mt = 0; mt < mts; ++mt)
+    for (int nt = 0; nt <= mt; ++nt) n += gram_tile(R, Bp, mt, nt) ? 1 : 0;
+  return n;
+}
+
+int gram_split_splits(int P, int K1, int K2, int Bp, int K) {
+  // about two workgroups per CU, at least two 64-wide chunks per split
+  const int64_t wgs = (int64_t)P * K2 * std::max(1, gram_tiles(K1, Bp));
+  const int nch = K / kKC;
+  int ks = (int)std::max<int64_t>(1, std::min<int64_t>((512 + wgs - 1) / wgs, nch / 2));
+  const int c = (nch + ks - 1) / ks;
+  return (nch + c - 1) / c;
+}
+
+void launch_gram_split(hipStream_t s, const float* X, int64_t ldx, int K, const int32_t* idx, float* gram, int P,
+                       int K1, int K2, int B, int Bp, int KSG, int xexp) {
+  const int nt = gram_tiles(K1, Bp), nch = K / kKC;
+  if (nt == 0) return;
+  launch(k_gram_split, (unsigned)((int64_t)P * K2 * nt * KSG), 512, 0, s, X, ldx, K, idx, gram, P, K1, K2, B, Bp, KSG,
+         (nch + KSG - 1) / KSG, nt, xexp);
 }
 
 }  // namespace hav

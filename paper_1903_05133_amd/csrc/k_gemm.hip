@@ -3,7 +3,7 @@
 // w <- w - lr * g), batched over the P learners and run on fp32 MFMA.
 //
 // k_fwd_nt:    part[ks][p][m][n] = sum_{k in split ks} A_p[m][k] * W_p[n][k]
-//              where fwd_split_takes says no (k_split.hip runs the others)
+//              where fwd_split_takes says no (k_delayed.hip runs the others)
 //              (A = gathered minibatch rows of X, or ReLU of the hidden
 //              pre-activations; W = a weight block, K-contiguous), split
 //              over K so the launch fills the GPU.  The consumer adds the

@@ -1,5 +1,5 @@
 """The wide contractions as split float32 products (csrc/split.h,
-csrc/k_split.hip): every tile of the forward and of the block update at its
+csrc/k_delayed.hip): every tile of the forward and of the block update at its
 edges, and operands of very different magnitudes, against the CPU oracle.
 
 Tolerance: the 1e-4 gate of the parity tests for whole parameter blocks.  For
