@@ -14,7 +14,9 @@ Also reported, on the same JSON line:
   roofline      the dominant kernel of the headline round (largest launches x
                 duration): algorithmic flops (or bytes) per launch over its
                 mean duration, timed with HIP events on the handle's stream
-                around a graph of back-to-back launches of it; `traffic` is the
+                around a graph of back-to-back launches of it, against the
+                matrix peak for float32 products as the kernel takes them (16-bit
+                peak over three or six products, or the float32 one); `traffic` is the
                 HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE
                 counters (profiles/traffic.json) while the kernel's source is
                 unchanged since they were taken
@@ -43,6 +45,11 @@ sys.path.insert(0, os.path.join(ROOT, "tests"))
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
+# A float32 product as three f16 products of two parts, or six bf16 products of
+# three: dense 16-bit matrix peak over the number of products.
+SPLIT2_PEAK_TFLOPS = 2500.0 / 3
+SPLIT3_PEAK_TFLOPS = 2500.0 / 6
+SPLIT2_CLASSES = ("fwd1_block_gemm", "fwd1_block_gemm_v", "block_update_gemm", "buffer_update_gemm")
 F = 4                          # bytes per float
 
 HEADLINE = "mlp_150528_1024_1000"
@@ -140,6 +147,14 @@ def kernel_work(c, classes=None):
     P, S, K1, K2 = c["P"], c["S"], c["K1"], c["K2"]
     if c["kind"] == "averaging":
         D = c["IN"]
+        G, T = P // S, K1 * K2
+        if T >= 2 and (S <= 8 or S in (16, 32)):
+            # all steps of a round in one launch: the common parameters (or
+            # every row), every given gradient and v read, v and the clusters'
+            # means written; then those means averaged
+            return {"momentum_first_step": (F * D * (1 + P * (T + 2) + G), 0),
+                    "momentum_group_mean": (F * D * (P * (T + 3) + G), 0),
+                    "momentum_global_mean": (F * D * (G + 1), 0)}
         return {
             # read w, v, g and write w, v of every learner
             "momentum": (20 * P * D, 0), "momentum_group_mean": (20 * P * D, 0),
@@ -181,6 +196,14 @@ def source_record(path, workload, kernel_class):
     except (OSError, KeyError, ValueError):
         return None
     return rec if cur == rec["source_sha256"] else None
+
+
+def mfma_peak(kernel, c):
+    """Matrix peak for float32 products as this kernel class takes them."""
+    if kernel in SPLIT2_CLASSES or (kernel == "gram" and c["B"] > 32):
+        return SPLIT2_PEAK_TFLOPS
+    wide = {"fwd1_gemm": c["H"] or c["C"], "fwd1_group_gemm": c["H"], "fwd2_gemm": c["C"]}
+    return SPLIT3_PEAK_TFLOPS if wide.get(kernel, 0) >= 64 else FP32_MFMA_PEAK_TFLOPS
 
 
 # ---------------------------------------------------------------- one workload
@@ -245,7 +268,7 @@ def summarize(name, c, ms_round, stats, dur_ms):
         kernels[k] = {"launches": n, "avg_us": round(avg * 1e3, 3), "share": round(tot / total, 4),
                       "GBps": round(b / (avg * 1e-3) / 1e9, 1) if b else None,
                       "TFLOPs": round(fl / (avg * 1e-3) / 1e12, 2) if fl else None,
-                      "mfma_frac": round(fl / (avg * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4) if fl else None,
+                      "mfma_frac": round(fl / (avg * 1e-3) / 1e12 / mfma_peak(k, c), 4) if fl else None,
                       "hbm_frac": round(b / (avg * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) if b else None}
     launches = sum(n for n, _ in stats.values())
     out = {"workload": name, "P": P, "S": c["S"], "K1": K1, "K2": K2, "ms_per_round": round(ms_round, 5),
@@ -262,7 +285,7 @@ def summarize(name, c, ms_round, stats, dur_ms):
     out.update({"B": c["B"], "lr": c["lr"], "N": c["N"], "learner_steps_per_round": steps,
                 "learner_steps_per_s": round(steps / (ms_round * 1e-3), 1),
                 "schedule": "delayed" if "fwd1_block_gemm" in stats else "eager",
-                "round_mfma_frac": round(steps * fl / (ms_round * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4),
+                "round_mfma_frac": round(steps * fl / (ms_round * 1e-3) / 1e12 / SPLIT2_PEAK_TFLOPS, 4),
                 "round_alg_bytes_frac": round(steps * by / (ms_round * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)})
     return out
 
@@ -276,10 +299,11 @@ def roofline(c, stats, dur_ms):
               key=lambda k: dur_ms[k] * stats[k][0])
     avg_s = dur_ms[dom] * 1e-3
     b, fl = work[dom]
-    if fl / (FP32_MFMA_PEAK_TFLOPS * 1e12) > b / (HBM_PEAK_GBS * 1e9):
+    peak = mfma_peak(dom, c)
+    if fl / (peak * 1e12) > b / (HBM_PEAK_GBS * 1e9):
         roof = {"kernel": dom, "bound": "mfma", "achieved": round(fl / avg_s / 1e12, 2),
-                "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(fl / avg_s / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4)}
+                "peak": round(peak, 1), "unit": "TFLOP/s",
+                "frac": round(fl / avg_s / 1e12 / peak, 4)}
     else:
         roof = {"kernel": dom, "bound": "hbm", "achieved": round(b / avg_s / 1e9, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(b / avg_s / 1e9 / HBM_PEAK_GBS, 4)}
@@ -288,7 +312,7 @@ def roofline(c, stats, dur_ms):
     roof.update({"traffic": None if tr is None else round(tr["bytes"]),
                  "alg_bytes_per_launch": round(b), "alg_flops_per_launch": fl, "avg_us": round(avg_s * 1e6, 3),
                  "hbm_frac": round(b / avg_s / 1e9 / HBM_PEAK_GBS, 4),
-                 "mfma_frac": round(fl / avg_s / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4) if fl else None,
+                 "mfma_frac": round(fl / avg_s / 1e12 / peak, 4) if fl else None,
                  "mfma_util_counter": None if mu is None else round(mu["mfma_util"], 4)})
     return roof
 
