@@ -660,8 +660,11 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   }
 }
 
-// Tiles of the block update: 256 x 256 in eight waves where the grid holds two
-// of them per CU and more (1024 x 150528, four groups of 512 rows: 2.36 ms =
+// Tiles of the block update: 256 x 256 in eight waves where they waste no units,
+// the contraction is 256 rows and more (a short one is the stream of W and the
+// buffers, which needs more workgroups per CU: 40 buffers of 128 x 8832, 32
+// rows, a whole job 6.6 ms in float32, 7.0 with this tile, 5.0 with 128 x 128,
+// 5.6 with 64 x 64) and the grid holds two of them per CU and more (1024 x 150528, four groups of 512 rows: 2.36 ms =
 // 268 TFLOP/s, as 128 x 256 in four waves; 128 x 128 2.6, the float32 MFMA
 // form 4.8; the chip's power limit sets the clock there); else 128 x 128
 // (512 x 3072, four groups: 38 us against 57 with 64 x 64 tiles, 66 in
@@ -681,7 +684,8 @@ void launch_block_update(hipStream_t s, const BlkArgs& a) {
     else                                                                                                       \
       launch(k_block_update<BM_, BN_, WM_, WN_, false, WPE_>, grid, th, 0, s, a, a.gtab, a.xtab, mt, nt);      \
   } while (0)
-  if (tiles(256, 256) >= 512)
+  const int R = a.K1 * a.SG * a.B;
+  if (a.Mrows % 256 == 0 && R >= 256 && tiles(256, 256) >= 512)
     HAV_BU(256, 256, 128, 64, 2);
   else if (tiles(128, 128) >= 256)
     HAV_BU(128, 128, 64, 64, 3);
