@@ -131,3 +131,27 @@ def test_non_finite_weights_stay_visible(value, gpu_lib):
         assert not np.isfinite(h.evaluate(0, 0, 64)[0])
         h.round()
         assert not h.finite()
+
+
+@pytest.mark.parametrize("rows", [2032, 2033, 4096, 4097])
+def test_evaluate_around_the_measured_form(rows, gpu_lib):
+    """Chunks of 2048 padded rows and more take W1's rows as two parts; ragged
+    widths, rows of W1 of very different magnitudes."""
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("mlp", 2, 1, 1, 1, B=16, IN=101, H=100, C=7, N=4200, sigma=0.5, lr=0.05, seed=231)
+    prob = cases.oracle_problem(c)
+    st = M.create(prob)
+    scale = 10.0 ** np.linspace(-6, 6, prob.H)
+    for p in range(prob.P):
+        b = M.unpack(prob, st.W[p])
+        b["W1"] *= scale[:, None]
+        b["W2"] /= scale[None, :]
+    w = st.W.astype(np.float32)
+    print(f"[gpu case] evaluate {rows}", flush=True)
+    with HierAvg(config=cases.native_config(c)) as h:
+        h.set_params(w)
+        for split in (0, 1):
+            loss, correct = h.evaluate(1, split, rows)
+            want, wc, gaps = M.evaluate(prob, w[1].astype(np.float64), np.arange(rows), split)
+            assert abs(loss - want) <= TOL * max(1.0, abs(want)), (loss, want)
+            assert abs(correct - wc) <= int(np.sum(gaps < 1e-5)), (correct, wc)
