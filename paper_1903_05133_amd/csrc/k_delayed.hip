@@ -618,27 +618,31 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
 #pragma unroll
         for (int r = 0; r < 16; ++r) x[r] = x[r] / (float)a.nbase;
       }
-      if (a.hb) {
+      // The change from the base (what the errors give, and c2 times the mean
+      // of B2) is summed first, so that the result is rounded to the base's
+      // precision once, in the fma that scales the base.
+      float d[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] *= c1;
-        if (a.B2) {
-          const float* b2 = a.B2 + (int64_t)g * a.b2_rows * a.b2_pitch;
-          float bm[16];
-          ld(b2, b, bm);
-          for (int c = 1; c < a.b2_rows; ++c) {
-            ld(b2 + (int64_t)c * a.b2_pitch, b, u);
+      for (int r = 0; r < 16; ++r) {
+        const int er = -a.xexp - gexp[wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3)];  // minus the scales
+        d[r] = c3 * __builtin_amdgcn_ldexpf(acc[i][j][r], er);
+      }
+      if (a.hb && a.B2) {
+        const float* b2 = a.B2 + (int64_t)g * a.b2_rows * a.b2_pitch;
+        float bm[16];
+        ld(b2, b, bm);
+        for (int c = 1; c < a.b2_rows; ++c) {
+          ld(b2 + (int64_t)c * a.b2_pitch, b, u);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) bm[r] += u[r];
-          }
-#pragma unroll
-          for (int r = 0; r < 16; ++r) x[r] += c2 * (bm[r] / (float)a.b2_rows);
+          for (int r = 0; r < 16; ++r) bm[r] += u[r];
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) d[r] += c2 * (bm[r] / (float)a.b2_rows);
       }
       const __amdgpu_buffer_rsrc_t rs = rsrc(a.Wo + (int64_t)g * a.wo_pitch, b);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int er = -a.xexp - gexp[wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3)];  // minus the scales
-        x[r] += c3 * __builtin_amdgcn_ldexpf(acc[i][j][r], er);
+        x[r] = __builtin_fmaf(c1, x[r], d[r]);
         const uint32_t m = __builtin_bit_cast(uint32_t, x[r]) & 0x7fffffffu;
         mx[r] = j == 0 ? m : max(mx[r], m);
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[r]), rs, voff, soff(b, r), 0);

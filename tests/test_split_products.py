@@ -155,3 +155,30 @@ def test_evaluate_around_the_measured_form(rows, gpu_lib):
             want, wc, gaps = M.evaluate(prob, w[1].astype(np.float64), np.arange(rows), split)
             assert abs(loss - want) <= TOL * max(1.0, abs(want)), (loss, want)
             assert abs(correct - wc) <= int(np.sum(gaps < 1e-5)), (correct, wc)
+
+
+def test_heavy_ball_block_end_rounds_the_parameters_once(gpu_lib):
+    """A heavy-ball block end adds the buffer's and the errors' share to the
+    block-start parameters.  The share is far below the parameters here (about
+    2^-9 of them), so its own rounding does not count, and n block ends leave
+    n roundings: errors of variance n/12 in units in the last place of the
+    parameter.  A second rounding per block end would give 2n/12; the line is
+    halfway.  One learner (means are exact), no decay (the base's coefficient
+    is exactly 1); the median over the hidden units keeps out units with a
+    ReLU decision at rounding."""
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("mlp", 1, 1, 4, 8, B=16, IN=256, H=64, C=5, N=300, sigma=0.5, momentum=0.875, lr=2.0 ** -14, seed=213)
+    prob = cases.oracle_problem(c)
+    st = M.create(prob)
+    print(f"[gpu case] {c}", flush=True)
+    with HierAvg(config=cases.native_config(c, "delayed")) as h:
+        for _ in range(2):
+            h.round()
+            M.hieravg_round(prob, st)
+        got = M.unpack(prob, h.params()[0].astype(np.float64))["W1"]
+    want = M.unpack(prob, st.W[0])["W1"]
+    ulps = (got - want) / np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
+    rms = np.sqrt(np.median((ulps ** 2).mean(axis=1)))
+    n = 2 * c["K2"]
+    print("rms", rms, "one rounding", np.sqrt(n / 12), flush=True)
+    assert rms <= np.sqrt(1.5 * n / 12), rms
