@@ -430,6 +430,76 @@ int64_t plan(hieravg* h, int B) {
   return std::max<int64_t>(ks_max * P * h->Bp * n1, mlp ? (int64_t)h->KS2 * P * h->Bp * h->Cp : 0);
 }
 
+// The padded sizes and the replica layout of a softmax or MLP handle.
+void set_dims(hieravg* h) {
+  const hieravg_config& c = h->cfg;
+  const bool mlp = c.kind == HIERAVG_KIND_MLP;
+  h->IN = c.in_dim;
+  h->C = c.classes;
+  h->H = mlp ? c.hidden : 0;
+  h->N = c.n_samples;
+  h->INp = round_up(h->IN, 64);
+  h->Cp = round_up(h->C, 16);
+  h->Hp = mlp ? round_up(h->H, 64) : 0;
+  if (mlp) {
+    h->off_W1 = 0;
+    h->off_b1 = h->Hp * h->INp;
+    h->off_W2 = h->off_b1 + h->Hp;
+    h->off_b2 = h->off_W2 + h->Cp * h->Hp;
+    h->Dp = round_up(h->off_b2 + h->Cp, 64);
+    h->D = h->H * h->IN + h->H + h->C * h->H + h->C;
+  } else {
+    h->off_W1 = 0;
+    h->off_b1 = h->Cp * h->INp;
+    h->Dp = round_up(h->off_b1 + h->Cp, 64);
+    h->D = h->C * h->IN + h->C;
+  }
+}
+
+// Floats that the buffers of a launch plan hold, and which buffers it has.
+struct PlanNeed {
+  int64_t part = 0, part2 = 0, partv = 0, gram = 0, errors = 0;  // errors: Gs, and Gu and Gt of heavy-ball blocks
+  bool delayed = false, hb = false, once = false;
+};
+
+// Plans minibatch size B and returns what that plan needs.
+PlanNeed plan_need(hieravg* h, int B) {
+  const hieravg_config& c = h->cfg;
+  const int64_t rows = (int64_t)c.P * round_up(B, 16);  // padded rows of one step
+  PlanNeed n;
+  n.part = plan(h, B);
+  n.once = h->once_cond;
+  if (h->delayed) {
+    n.delayed = true;
+    n.hb = h->hb;
+    n.errors = c.K1 * rows * h->Hp;
+    n.gram = (int64_t)h->KSG * c.K2 * c.K1 * c.K1 * rows * h->Bp;
+    n.part2 = h->KS2 * rows * h->Cp;
+    if (h->hb) n.partv = h->KSv * c.K1 * rows * h->Hp;
+  }
+  return n;
+}
+
+// What every minibatch size up to Bmax needs (hieravg_set_batch may take any).
+// Every size is planned: the schedule depends on B itself (K1 * S * B rows at
+// most), so a size may be delayed, with its rows padded to 16, where the next
+// multiple of 16 is not.
+PlanNeed plan_need_upto(hieravg* h, int Bmax) {
+  PlanNeed m;
+  for (int b = 1; b <= Bmax; ++b) {
+    const PlanNeed n = plan_need(h, b);
+    m.part = std::max(m.part, n.part);
+    m.part2 = std::max(m.part2, n.part2);
+    m.partv = std::max(m.partv, n.partv);
+    m.gram = std::max(m.gram, n.gram);
+    m.errors = std::max(m.errors, n.errors);
+    m.delayed = m.delayed || n.delayed;
+    m.hb = m.hb || n.hb;
+    m.once = m.once || n.once;
+  }
+  return m;
+}
+
 // The magnitude tables within h->mags.
 MagTables mag_tables(const hieravg* h) {
   MagTables m;
@@ -518,50 +588,11 @@ int build(hieravg* h) {
     HAV_CHECK(hipMemcpyAsync(h->Wm, h->W, sizeof(float) * h->Dp, hipMemcpyDeviceToDevice, h->stream));
   } else {
     const bool mlp = c.kind == HIERAVG_KIND_MLP;
-    h->IN = c.in_dim;
-    h->C = c.classes;
-    h->H = mlp ? c.hidden : 0;
-    h->N = c.n_samples;
-    h->INp = round_up(h->IN, 64);
-    h->Cp = round_up(h->C, 16);
-    h->Hp = mlp ? round_up(h->H, 64) : 0;
-    if (mlp) {
-      h->off_W1 = 0;
-      h->off_b1 = h->Hp * h->INp;
-      h->off_W2 = h->off_b1 + h->Hp;
-      h->off_b2 = h->off_W2 + h->Cp * h->Hp;
-      h->Dp = round_up(h->off_b2 + h->Cp, 64);
-      h->D = h->H * h->IN + h->H + h->C * h->H + h->C;
-    } else {
-      h->off_W1 = 0;
-      h->off_b1 = h->Cp * h->INp;
-      h->Dp = round_up(h->off_b1 + h->Cp, 64);
-      h->D = h->C * h->IN + h->C;
-    }
+    set_dims(h);
     const int T = h->T;
-    // Buffers hold the largest launch plan over every batch size up to the
-    // create-time B (hieravg_set_batch may lower it).
     h->Bmax = c.B;
-    int64_t part_floats = 0, part2_floats = 0, partv_floats = 0;
-    bool any_delayed = false, any_hb = false, any_once = false;
-    int Bp_del = 0;
-    int64_t gram_floats = 0;
-    for (int b = 16; b <= round_up(c.B, 16); b += 16) {
-      const int64_t pf = plan(h, std::min(b, c.B));
-      part_floats = std::max(part_floats, pf);
-      any_once = any_once || h->once_cond;
-      if (h->delayed) {
-        any_delayed = true;
-        any_hb = any_hb || h->hb;
-        Bp_del = std::max(Bp_del, h->Bp);
-        gram_floats = std::max<int64_t>(gram_floats,
-                                        (int64_t)h->KSG * c.K2 * P * c.K1 * c.K1 * h->Bp * h->Bp);
-        part2_floats = std::max<int64_t>(part2_floats, (int64_t)h->KS2 * P * h->Bp * h->Cp);
-        if (h->hb) partv_floats = std::max<int64_t>(partv_floats, (int64_t)h->KSv * c.K1 * P * h->Bp * h->Hp);
-      }
-    }
+    const PlanNeed need = plan_need_upto(h, c.B);
     plan(h, c.B);
-    h->Bp = (int)round_up(c.B, 16);
     int rc;
     if ((rc = alloc_zero(h, (void**)&h->W, sizeof(float) * P * h->Dp, "replicas"))) return rc;
     if (c.momentum > 0.0f &&
@@ -570,7 +601,7 @@ int build(hieravg* h) {
     if ((rc = alloc_zero(h, (void**)&h->X, sizeof(float) * h->N * h->INp, "dataset"))) return rc;
     if ((rc = alloc_zero(h, (void**)&h->y, sizeof(int32_t) * h->N, "labels"))) return rc;
     if ((rc = alloc_zero(h, (void**)&h->idx, sizeof(int32_t) * (size_t)T * P * c.B, "indices"))) return rc;
-    if ((rc = alloc_zero(h, (void**)&h->part, sizeof(float) * part_floats, "split-K partials"))) return rc;
+    if ((rc = alloc_zero(h, (void**)&h->part, sizeof(float) * need.part, "split-K partials"))) return rc;
     if ((rc = alloc_zero(h, (void**)&h->G2, sizeof(float) * P * h->Bp * h->Cp, "output error"))) return rc;
     if (mlp && h->C <= kSmallC &&
         (rc = alloc_zero(h, (void**)&h->PL, sizeof(float) * 2 * P * (h->Hp / 32) * h->Bp * h->Cp, "partial logits")))
@@ -578,7 +609,7 @@ int build(hieravg* h) {
     if (mlp) {
       if ((rc = alloc_zero(h, (void**)&h->Z1, sizeof(float) * P * h->Bp * h->Hp, "hidden activations"))) return rc;
       if ((rc = alloc_zero(h, (void**)&h->G1, sizeof(float) * P * h->Bp * h->Hp, "hidden error"))) return rc;
-      if (any_once) {
+      if (need.once) {
         const size_t w1 = sizeof(float) * h->Hp * h->INp;
         if ((rc = alloc_zero(h, (void**)&h->Wg, w1, "common first layer")) ||
             (c.S > 1 && (rc = alloc_zero(h, (void**)&h->Wc, w1 * (P / c.S), "cluster copies of W1"))))
@@ -593,19 +624,19 @@ int build(hieravg* h) {
       }
     }
     if ((rc = alloc_zero(h, (void**)&h->ctr, 2 * sizeof(uint64_t), "counters"))) return rc;
-    if (any_delayed) {
+    if (need.delayed) {
       const int64_t w1 = h->Hp * h->INp;
       if (!h->Wc && (rc = alloc_zero(h, (void**)&h->Wc, sizeof(float) * (P / c.S) * w1, "cluster copies of W1")))
         return rc;
-      if ((rc = alloc_zero(h, (void**)&h->Gs, sizeof(float) * c.K1 * P * Bp_del * h->Hp, "block errors"))) return rc;
-      if (any_hb) {
+      if ((rc = alloc_zero(h, (void**)&h->Gs, sizeof(float) * need.errors, "block errors"))) return rc;
+      if (need.hb) {
         if ((rc = alloc_zero(h, (void**)&h->Wc2, sizeof(float) * (P / c.S) * w1, "second cluster copies of W1")) ||
-            (rc = alloc_zero(h, (void**)&h->Gu, sizeof(float) * c.K1 * P * Bp_del * h->Hp, "scaled block errors")))
+            (rc = alloc_zero(h, (void**)&h->Gu, sizeof(float) * need.errors, "scaled block errors")))
           return rc;
         if (c.momentum > 0.0f) {
           const int64_t rp1 = round_up((int64_t)c.K1 * c.B, 32);
-          if ((rc = alloc_zero(h, (void**)&h->Gt, sizeof(float) * c.K1 * P * Bp_del * h->Hp, "buffer block errors")) ||
-              (rc = alloc_zero(h, (void**)&h->partv, sizeof(float) * partv_floats, "buffer partials")) ||
+          if ((rc = alloc_zero(h, (void**)&h->Gt, sizeof(float) * need.errors, "buffer block errors")) ||
+              (rc = alloc_zero(h, (void**)&h->partv, sizeof(float) * need.partv, "buffer partials")) ||
               (rc = alloc_zero(h, (void**)&h->btab1, 2 * sizeof(uint32_t) * (size_t)c.K2 * P * rp1,
                                "buffer update row tables")))
             return rc;
@@ -616,14 +647,14 @@ int build(hieravg* h) {
       if ((rc = alloc_zero(h, (void**)&h->btab, 2 * sizeof(uint32_t) * (size_t)c.K2 * (P / c.S) * rp,
                            "block update row tables")))
         return rc;
-      const int64_t mag_n = h->Hp * (1 + 2 * (int64_t)c.K2 * (P / c.S) + (any_hb && h->V ? P * (1 + (int64_t)c.K2) : 0));
+      const int64_t mag_n = h->Hp * (1 + 2 * (int64_t)c.K2 * (P / c.S) + (need.hb && h->V ? P * (1 + (int64_t)c.K2) : 0));
       if ((rc = alloc_zero(h, (void**)&h->mags, sizeof(uint32_t) * mag_n, "magnitude tables"))) return rc;
       // more than 32 classes: the layer-2 partials of a step must not overwrite
       // the block forward's partials of the later steps
       if (h->C > kSmallC &&
-          (rc = alloc_zero(h, (void**)&h->part2, sizeof(float) * part2_floats, "layer-2 partials")))
+          (rc = alloc_zero(h, (void**)&h->part2, sizeof(float) * need.part2, "layer-2 partials")))
         return rc;
-      if (c.K1 > 1 && (rc = alloc_zero(h, (void**)&h->gram, sizeof(float) * gram_floats, "Gram blocks"))) return rc;
+      if (c.K1 > 1 && (rc = alloc_zero(h, (void**)&h->gram, sizeof(float) * need.gram, "Gram blocks"))) return rc;
     }
     plan(h, c.B);  // again, now that the buffers of the once-written means exist
     h->key_index = hash64(seed, kTagIndex);

@@ -182,3 +182,27 @@ def test_heavy_ball_block_end_rounds_the_parameters_once(gpu_lib):
     n = 2 * c["K2"]
     print("rms", rms, "one rounding", np.sqrt(n / 12), flush=True)
     assert rms <= np.sqrt(1.5 * n / 12), rms
+
+
+@pytest.mark.parametrize("c,B", [
+    # K1 * S * B = 15776 rows at 116 samples: delayed; 17408 at the padded 128 and at create's B: not
+    (cases.case("mlp", 17, 17, 8, 1, B=128, IN=600, H=1000, C=10, N=500, sigma=0.5, lr=0.02, seed=214), 116),
+    # the same up to 32 samples: 12000 rows at 20, 19200 at the padded 32
+    (cases.case("mlp", 75, 75, 8, 1, B=32, IN=200, H=510, C=3, N=500, sigma=0.5, lr=0.02, seed=215), 20),
+], ids=["wide", "narrow"])
+def test_set_batch_into_the_delayed_schedule(c, B, gpu_lib):
+    """A minibatch whose round is delayed on a handle whose create-time and
+    padded minibatches are not: its buffers hold the padded rows."""
+    from paper_1903_05133_amd import HierAvg
+    from dataclasses import replace
+    prob = replace(cases.oracle_problem(c), B=B)
+    st = M.create(prob)
+    print(f"[gpu case] set_batch {B} {c}", flush=True)
+    with HierAvg(config=cases.native_config(c)) as h:
+        h.set_batch(B)
+        h.profile(True)
+        h.round()
+        assert "fwd1_block_gemm" in h.profile_read()
+        M.hieravg_round(prob, st)
+        ok, det = cases.parity_report(prob, h.params(), st.W)
+        assert ok, det
