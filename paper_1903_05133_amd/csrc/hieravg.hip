@@ -427,6 +427,10 @@ int64_t plan(hieravg* h, int B) {
       plan_split(P, c.K1 * h->Bp, (int)h->Hp, (int)h->INp, &h->KSv, &h->cpsv);
   }
   h->ks_cur = h->KS1;
+  // What the last round ran, for hieravg_time_kernel, as far as this plan has
+  // it: the launches of another schedule would not fit this one's buffers.
+  h->in_delayed = h->in_delayed && h->delayed;
+  h->in_wg = h->in_wg && h->once_global;
   return std::max<int64_t>(ks_max * P * h->Bp * n1, mlp ? (int64_t)h->KS2 * P * h->Bp * h->Cp : 0);
 }
 

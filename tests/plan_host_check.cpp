@@ -35,7 +35,14 @@ void check(const hieravg_config& c) {
   const PlanNeed have = plan_need_upto(h, c.B);
   h->once_alloc = have.once;
   for (int B = 1; B <= c.B; ++B) {
+    // as after a round of another minibatch size, delayed or from the common copy
+    h->in_delayed = h->in_wg = true;
     const PlanNeed n = plan_need(h, B);
+    if ((h->in_delayed && !n.delayed) || (h->in_wg && !n.once)) {
+      ++fails;
+      std::printf("FAIL B %d of %d keeps the schedule of the round before\n", B, c.B);
+      return;
+    }
     ++checked;
     delayed_plans += n.delayed ? 1 : 0;
     const bool ok = n.part <= have.part && n.part2 <= have.part2 && n.partv <= have.partv && n.gram <= have.gram &&
