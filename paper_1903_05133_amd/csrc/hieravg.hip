@@ -1111,7 +1111,7 @@ bool launch_class(hieravg* h, int kc, int tt) {
     }
     case KC_HEAD_STEP:
     case KC_HEAD_END: {
-      if (!h->in_delayed) return false;
+      if (!small || !h->in_delayed || h->wide) return false;
       // HEAD_STEP at step tt: backward of step tt-1 of the block (if any),
       // forward and output error of step tt; HEAD_END at a block's last step
       // tt: its backward.
@@ -2200,6 +2200,9 @@ int hieravg_time_kernel(hieravg_t h, int kernel_class, int reps, double* mean_ms
   // stays out of the timed interval.
   HAV_CHECK(hipStreamSynchronize(h->stream));
   if (h->delayed && !h->mags_valid) HAV_CHECK(measure_mags(h));
+  // The partials of a delayed round: replayed rounds leave the count of the
+  // round captured last, which may be an eager one's.
+  if (h->in_delayed) h->ks_cur = h->KS_b;
   HAV_CHECK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
   bool ok = true;
   for (int i = 0; i < reps && ok; ++i) ok = launch_class(h, kernel_class, 0);

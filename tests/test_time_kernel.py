@@ -1,0 +1,52 @@
+"""hieravg_time_kernel: every class of a workload can be timed on its own, a
+class that the workload does not launch is refused, and what the launches
+leave behind is the state of extra applications of the kernel."""
+
+import numpy as np
+import pytest
+
+import cases
+
+pytestmark = pytest.mark.gpu
+
+
+def _handle(c, mode="auto"):
+    from paper_1903_05133_amd import HierAvg
+    print(f"[gpu case] time_kernel {mode} {c}", flush=True)
+    return HierAvg(config=cases.native_config(c, mode))
+
+
+WIDE = cases.case("mlp", 4, 2, 2, 2, B=48, IN=1100, H=500, C=7, N=300, sigma=0.5, lr=0.01, seed=501)
+
+
+@pytest.mark.parametrize("c,refused", [
+    # more than 32 samples, more than 32 classes: no k_head_step
+    (WIDE, ("head_step", "head_step_end")),
+    (dict(WIDE, B=20, C=40), ("head_step", "head_step_end", "head_fused")),
+    (dict(WIDE, B=20), ("z1_delayed", "b1_step")),
+], ids=["wide", "many_classes", "narrow"])
+def test_classes_of_other_heads_are_refused(c, refused, gpu_lib):
+    with _handle(c) as h:
+        h.profile(True)
+        h.round()
+        ran = set(h.profile_read()) - {"draw_indices"}
+        h.profile(False)
+        for name in refused:
+            with pytest.raises(Exception):
+                h.time_kernel(name, 1)
+        for name in sorted(ran):
+            assert h.time_kernel(name, 2) > 0.0
+
+
+def test_head_step_after_an_eager_round(gpu_lib):
+    """A replayed delayed round after an eager one: the head reads the block
+    forward's partials in their own split count."""
+    with _handle(dict(WIDE, B=20)) as h:
+        h.round()
+        w = h.params()
+        w[1, 0] += 1.0
+        h.set_params(w)  # rows that differ: the next round is eager
+        h.round()
+        h.round()
+        assert h.time_kernel("head_step", 3) > 0.0
+        assert h.finite()
