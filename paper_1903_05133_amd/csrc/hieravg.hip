@@ -1743,11 +1743,8 @@ int hieravg_round(hieravg_t h) {
                                hipMemcpyDeviceToDevice, h->stream));
     h->rows_stale = false;
   }
-  if (h->in_delayed && !h->mags_valid) {
-    HAV_CHECK(measure_mags(h));
-    h->mags_valid = true;
-  }
-  if (!h->in_delayed) h->mags_valid = false;
+  if (h->in_delayed && !h->mags_valid) HAV_CHECK(measure_mags(h));
+  h->mags_valid = false;  // until the round is enqueued
   h->launch_failed = false;
   const char* refused = "a step launch of the round's plan was refused (internal error)";
   if (h->profiling) {
@@ -1779,6 +1776,7 @@ int hieravg_round(hieravg_t h) {
     set_error(refused);
     return HIERAVG_EINVAL;
   }
+  h->mags_valid = h->in_delayed;
   // After the global mean every learner holds replica 0's W1 (under delayed
   // updates only replica 0's copy is written); averaging kind: Wm holds every
   // learner's parameters (with P = 1 the round's last step writes row 0).
@@ -2199,7 +2197,16 @@ int hieravg_time_kernel(hieravg_t h, int kernel_class, int reps, double* mean_ms
   // is launched once between the two events, so the host's per-launch cost
   // stays out of the timed interval.
   HAV_CHECK(hipStreamSynchronize(h->stream));
-  if (h->delayed && !h->mags_valid) HAV_CHECK(measure_mags(h));
+  if (h->delayed) {
+    // The launches are step 0's: the scales of the parameters as they are now
+    // (the tables hold the last round's start), and, for the errors that the
+    // last block left, the largest of every block in the first one's place.
+    HAV_CHECK(measure_mags(h));
+    const MagTables m = mag_tables(h);
+    launch_fold_maxima(h->stream, m.g, m.G * m.Hp, m.K2);
+    HAV_CHECK(hipGetLastError());
+    h->mags_valid = false;  // and again at the next round: a launch may change what was measured
+  }
   // The partials of a delayed round: replayed rounds leave the count of the
   // round captured last, which may be an eager one's.
   if (h->in_delayed) h->ks_cur = h->KS_b;

@@ -230,6 +230,8 @@ struct MagTables {
 // [mats][nrows].
 void launch_row_maxima(hipStream_t s, const float* W, int64_t w_pitch, int64_t ld, int64_t n, int nrows, int mats,
                        uint32_t* out);
+// t[i] = the largest of t[b * len + i], b < n, for i < len.
+void launch_fold_maxima(hipStream_t s, uint32_t* t, int64_t len, int n);
 // ylab (optional): the label of every drawn sample, same layout as idx.
 // mag.w0 (optional): also start the round's magnitude tables.
 // tables.gtab (optional): also write the block update's row tables.

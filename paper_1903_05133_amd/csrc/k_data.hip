@@ -197,4 +197,16 @@ void launch_row_maxima(hipStream_t s, const float* W, int64_t w_pitch, int64_t l
   launch(k_row_maxima, (unsigned)((int64_t)nrows * mats), 256, 0, s, W, w_pitch, ld, n, nrows, out);
 }
 
+__global__ __launch_bounds__(256) void k_fold_maxima(uint32_t* __restrict__ t, int64_t len, int n) {
+  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256) {
+    uint32_t m = t[i];
+    for (int b = 1; b < n; ++b) m = max(m, t[b * len + i]);
+    t[i] = m;
+  }
+}
+
+void launch_fold_maxima(hipStream_t s, uint32_t* t, int64_t len, int n) {
+  launch(k_fold_maxima, grid_for(len, 1024), 256, 0, s, t, len, n);
+}
+
 }  // namespace hav

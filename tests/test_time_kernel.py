@@ -50,3 +50,43 @@ def test_head_step_after_an_eager_round(gpu_lib):
         h.round()
         assert h.time_kernel("head_step", 3) > 0.0
         assert h.finite()
+
+
+@pytest.mark.parametrize("c", [WIDE, dict(WIDE, B=20), dict(WIDE, B=20, C=40), dict(WIDE, B=20, momentum=0.9)],
+                         ids=["wide", "narrow", "many_classes", "momentum"])
+def test_rounds_after_timing_every_class(c, gpu_lib):
+    """The launches scale the products by the operands as they are: timing
+    every class of a delayed round leaves finite parameters, and so does the
+    round after it."""
+    with _handle(c) as h:
+        h.profile(True)
+        h.round()
+        ran = set(h.profile_read()) - {"draw_indices"}
+        h.profile(False)
+        for name in sorted(ran):
+            h.time_kernel(name, 2)
+            assert h.finite(), name
+        h.round()
+        assert h.finite()
+
+
+def test_block_end_of_errors_that_grew(gpu_lib):
+    """A unit that no sample activates in the first block and every sample does
+    in the second: its first block's errors are zero, those that a block-end
+    launch finds are the second's.  Also buffers that grow far beyond the
+    round's by repeated launches."""
+    c = dict(WIDE, K1=1, B=20, momentum=0.9)
+    with _handle(c) as h:
+        u, IN, H = 3, c["IN"], c["H"]
+        w, v = h.params(), h.momentum()
+        w[:, u * IN:(u + 1) * IN] = 0.0  # z = b1 = 0 at step 0 (not active), b1 > 0 at step 1
+        v[:, H * IN + u] = -1.0
+        h.set_params(w)
+        h.set_momentum(v)
+        h.round()
+        for name in ("scale_errors", "buffer_update_gemm", "block_update_gemm"):
+            h.time_kernel(name, 1)
+            assert h.finite() and np.isfinite(h.momentum()).all(), name
+        h.time_kernel("buffer_update_gemm", 30)
+        h.round()
+        assert h.finite() and np.isfinite(h.momentum()).all()
