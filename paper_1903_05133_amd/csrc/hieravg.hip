@@ -722,22 +722,18 @@ bool launch_class(hieravg* h, int kc, int tt) {
     if (h->avg_round) {
       // Every step of the round in one launch (from Wm, or from every row),
       // the clusters' means to their first rows; then their mean to Wm.  One
-      // cluster writes Wm itself (one learner its row).
+      // cluster writes Wm itself (one learner its row).  The classes that
+      // such a round does not launch stay the steps' own (hieravg_time_kernel).
       const bool one = P == S;
-      switch (kc) {
-        case KC_MOMENTUM_FIRST:
-        case KC_MOMENTUM_GROUP:
-          if ((kc == KC_MOMENTUM_FIRST) != h->in_shared) return false;
-          launch_avg_round(s, h->in_shared ? h->Wm : W, h->in_shared ? 0 : h->Dp, h->V, h->Gr, h->Dp, P, S, h->T,
-                           c.K1, h->hyper, c.momentum, c.weight_decay, c.avg_momentum != 0,
-                           one && P > 1 ? h->Wm : W, (int64_t)S * h->Dp);
-          return true;
-        case KC_MOMENTUM_GLOBAL:
-          if (one) return false;
-          launch_mean_rows(s, h->Wm, W, (int64_t)S * h->Dp, h->Dp, P / S);
-          return true;
-        case KC_VMEAN_GLOBAL: launch_group_mean(s, h->V, h->Dp, h->Dp, P, P); return true;
-        default: return false;
+      if (kc == (h->in_shared ? KC_MOMENTUM_FIRST : KC_MOMENTUM_GROUP)) {
+        launch_avg_round(s, h->in_shared ? h->Wm : W, h->in_shared ? 0 : h->Dp, h->V, h->Gr, h->Dp, P, S, h->T, c.K1,
+                         h->hyper, c.momentum, c.weight_decay, c.avg_momentum != 0, one && P > 1 ? h->Wm : W,
+                         (int64_t)S * h->Dp);
+        return true;
+      }
+      if (kc == KC_MOMENTUM_GLOBAL && !one) {
+        launch_mean_rows(s, h->Wm, W, (int64_t)S * h->Dp, h->Dp, P / S);
+        return true;
       }
     }
     switch (kc) {

@@ -90,3 +90,23 @@ def test_block_end_of_errors_that_grew(gpu_lib):
         h.time_kernel("buffer_update_gemm", 30)
         h.round()
         assert h.finite() and np.isfinite(h.momentum()).all()
+
+
+@pytest.mark.parametrize("P,S", [(4, 2), (4, 4), (1, 1)])
+def test_step_classes_of_averaging_rounds(P, S, gpu_lib):
+    """Rounds that take all their steps in one launch: the classes of single
+    steps and of the buffers' means can still be timed, before a round and
+    after one, and a step is one step."""
+    c = cases.case("averaging", P, S, 2, 2, IN=300, lr=0.5, momentum=0.9, avg_momentum=True, seed=502)
+    with _handle(c) as h:
+        for _ in range(2):
+            names = ["momentum", "momentum_group_mean", "momentum_global_mean", "momentum_buffer_group_mean",
+                     "momentum_buffer_global_mean"]
+            for name in names:
+                assert h.time_kernel(name, 2) > 0.0
+            assert h.finite()
+            h.round()
+    with _handle(c) as h:
+        w = h.params()
+        h.time_kernel("momentum", 1)  # one heavy-ball step of the given gradients from v = 0: w - lr v
+        assert np.allclose(h.params(), w - np.float32(0.5) * h.momentum(), rtol=0, atol=1e-7)
