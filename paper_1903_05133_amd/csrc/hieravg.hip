@@ -511,12 +511,13 @@ MagTables mag_tables(const hieravg* h) {
   m.G = h->cfg.P / h->cfg.S;
   m.Hp = (int)h->Hp;
   m.P = h->cfg.P;
-  const int64_t blk = (int64_t)m.K2 * m.G * m.Hp;
+  const bool buffers = h->hb && h->V;
+  m.gS = buffers ? 1 : h->cfg.S;
   m.w0 = h->mags;
   m.w = m.w0 + m.Hp;
-  m.g = m.w + blk;
-  if (h->hb && h->V) {
-    m.v0 = m.g + blk;
+  m.g = m.w + (int64_t)m.K2 * m.G * m.Hp;
+  if (buffers) {
+    m.v0 = m.g + m.g_block() * m.K2;
     m.v = m.v0 + (int64_t)m.P * m.Hp;
   }
   return m;
@@ -651,7 +652,9 @@ int build(hieravg* h) {
       if ((rc = alloc_zero(h, (void**)&h->btab, 2 * sizeof(uint32_t) * (size_t)c.K2 * (P / c.S) * rp,
                            "block update row tables")))
         return rc;
-      const int64_t mag_n = h->Hp * (1 + 2 * (int64_t)c.K2 * (P / c.S) + (need.hb && h->V ? P * (1 + (int64_t)c.K2) : 0));
+      // w0, w and g, or with buffers also v0 and v and a g of every learner
+      const int64_t copies = (int64_t)c.K2 * (P / c.S), own = (int64_t)c.K2 * P;
+      const int64_t mag_n = h->Hp * (1 + copies + (need.hb && h->V ? P + 2 * own : copies));
       if ((rc = alloc_zero(h, (void**)&h->mags, sizeof(uint32_t) * mag_n, "magnitude tables"))) return rc;
       // more than 32 classes: the layer-2 partials of a step must not overwrite
       // the block forward's partials of the later steps
@@ -961,8 +964,7 @@ bool launch_class(hieravg* h, int kc, int tt) {
       a.b2_pitch = h->Dp;
       a.b2_rows = 1;
       const MagTables mg = mag_tables(h);
-      a.gmax = mg.g + (int64_t)b * mg.G * Hp;
-      a.gm_div = S;
+      a.gmax = mg.g + b * mg.g_block();
       a.xexp = x_exp(h);
       a.hb_g = hb_index(HB_T, 0);
       a.wmax_out = mg.v + (int64_t)b * P * Hp;
@@ -987,12 +989,13 @@ bool launch_class(hieravg* h, int kc, int tt) {
         }
       }
       const MagTables mg = mag_tables(h);
-      a.gmax = mg.g + (int64_t)b * mg.G * Hp;
+      a.gmax = mg.g + b * mg.g_block();
+      a.gm_n = S / mg.gS;
       a.xexp = x_exp(h);
       a.hb_g = hb_index(HB_U, 0);
       a.wmax_out = mg.w + (int64_t)b * mg.G * Hp;
       if (b == c.K2 - 1 && h->global_last) {
-        a.gm_n = mg.G;
+        a.gm_n = P / mg.gS;
         // The last block: one update over all P learners from the mean of the
         // cluster copies (the global mean of Algorithm 1, which skips the
         // cluster mean before it), into replica 0's W1, and the global mean
@@ -1096,8 +1099,9 @@ bool launch_class(hieravg* h, int kc, int tt) {
           a.KS = 1;
         }
         a.G1 = h->Gs + (int64_t)k * P * Bp * Hp;
-        a.gmax = mag_tables(h).g + (int64_t)(tt / c.K1) * (P / S) * Hp;
-        a.gS = S;
+        const MagTables mg = mag_tables(h);
+        a.gmax = mg.g + tt / c.K1 * mg.g_block();
+        a.gS = mg.gS;
       }
       if (kc == KC_HEAD_FUSED)
         launch_head_fused(s, a);
@@ -1148,8 +1152,9 @@ bool launch_class(hieravg* h, int kc, int tt) {
           a.vb2 = h->V + h->off_b2;
         }
       }
-      a.gmax = mag_tables(h).g + (int64_t)blk * (P / S) * Hp;
-      a.gS = S;
+      const MagTables mg = mag_tables(h);
+      a.gmax = mg.g + blk * mg.g_block();
+      a.gS = mg.gS;
       launch_head_step(s, a, k);
       return true;
     }
@@ -1164,8 +1169,9 @@ bool launch_class(hieravg* h, int kc, int tt) {
       launch_fwd(s, f, A_RELU);
       return true;
     }
-    case KC_BWD_HIDDEN:
+    case KC_BWD_HIDDEN: {
       if (small) return false;
+      const MagTables mg = h->in_delayed ? mag_tables(h) : MagTables();
       if (h->in_delayed && h->wide)  // b1 takes its step in KC_B1_STEP
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->Gs + (int64_t)(tt % c.K1) * P * Bp * Hp, P, B,
                           Bp, C, Cp, Hp);
@@ -1174,18 +1180,21 @@ bool launch_class(hieravg* h, int kc, int tt) {
                           Bp, C, Cp, Hp, W + h->off_b1, h->hyper, h->hb && h->V ? h->V + h->off_b1 : nullptr,
                           h->hb ? c.momentum : 0.0f, h->hb ? c.weight_decay : 0.0f,
                           h->w2_fused ? W + h->off_b2 : nullptr,
-                          mag_tables(h).g + (int64_t)(tt / c.K1) * (P / S) * Hp, S);
+                          mg.g + tt / c.K1 * mg.g_block(), mg.gS);
       else if (h->w2_fused)
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->G1, P, B, Bp, C, Cp, Hp, nullptr, h->hyper,
                           nullptr, 0.0f, 0.0f, W + h->off_b2);
       else
         launch_bwd_hidden(s, h->G2, W + h->off_W2, h->Dp, h->Z1, h->G1, P, B, Bp, C, Cp, Hp);
       return true;
-    case KC_B1_STEP:
+    }
+    case KC_B1_STEP: {
       if (!h->in_delayed || !h->wide || small) return false;
+      const MagTables mg = mag_tables(h);
       launch_b1_step(s, h->Gs + (int64_t)(tt % c.K1) * P * Bp * Hp, W + h->off_b1, h->Dp, h->hyper, P, B, Bp, Hp,
-                     mag_tables(h).g + (int64_t)(tt / c.K1) * (P / S) * Hp, S);
+                     mg.g + tt / c.K1 * mg.g_block(), mg.gS);
       return true;
+    }
     case KC_Z1_DELAYED: {
       if (!h->in_delayed || (small && !h->wide)) return false;
       Z1Args a{};
@@ -2199,7 +2208,7 @@ int hieravg_time_kernel(hieravg_t h, int kernel_class, int reps, double* mean_ms
     // last block left, the largest of every block in the first one's place.
     HAV_CHECK(measure_mags(h));
     const MagTables m = mag_tables(h);
-    launch_fold_maxima(h->stream, m.g, m.G * m.Hp, m.K2);
+    launch_fold_maxima(h->stream, m.g, m.g_block(), m.K2);
     HAV_CHECK(hipGetLastError());
     h->mags_valid = false;  // and again at the next round: a launch may change what was measured
   }

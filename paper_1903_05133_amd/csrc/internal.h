@@ -217,13 +217,16 @@ struct BlkTables {
 // scales of their f16 parts (split.h).  w0: rows of W1 at the round start;
 // w: rows of the cluster copies written by each block's update ([K2][G][Hp],
 // the last block's global result in its first entry); g: hidden units of the
-// block's errors ([K2][G][Hp], by cluster); v0, v (with buffers): rows of the
-// learners' buffers, [P][Hp] and [K2][P][Hp].  A round starts by taking w0
-// and v0 from the last block's entries and clearing the rest; the kernels
-// that write an operand raise its entries.
+// block's errors ([K2][P/gS][Hp]: of a cluster's learners together, or, with
+// buffers, of each learner, whose own buffer is updated from its errors
+// alone); v0, v (with buffers): rows of the learners' buffers, [P][Hp] and
+// [K2][P][Hp].  A round starts by taking w0 and v0 from the last block's
+// entries and clearing the rest; the kernels that write an operand raise its
+// entries.
 struct MagTables {
   uint32_t *w0 = nullptr, *w = nullptr, *g = nullptr, *v0 = nullptr, *v = nullptr;
-  int K2 = 0, G = 0, Hp = 0, P = 0;
+  int K2 = 0, G = 0, Hp = 0, P = 0, gS = 1;
+  __host__ __device__ int64_t g_block() const { return (int64_t)(P / gS) * Hp; }  // g's entries of a block
 };
 // out[r] = the largest magnitude of row r of W (ld floats apart, n a multiple
 // of 4), rows r < nrows of `mats` matrices w_pitch floats apart; out is
@@ -350,12 +353,12 @@ struct BlkArgs {
   int64_t b2_pitch = 0;
   int b2_rows = 0;
   // Magnitudes: the error rows' largest per unit, as float bits [..][Mrows]:
-  // group g takes the larger of entries (g/gm_div)*gm_n .. +gm_n-1 (before
-  // the coefficients hb[hb_g + k] that scaled errors carry); xexp as in
+  // group g takes the largest of entries g*gm_n .. +gm_n-1 (before the
+  // coefficients hb[hb_g + k] that scaled errors carry); xexp as in
   // FwdArgs.  wmax_out (optional, [P/SG][Mrows]): raised to the largest
   // magnitude of each result row.
   const uint32_t* gmax = nullptr;
-  int gm_div = 1, gm_n = 1, xexp = 0, hb_g = 0;
+  int gm_n = 1, xexp = 0, hb_g = 0;
   uint32_t* wmax_out = nullptr;
 };
 // Largest contraction (K1 * SG * B rows) of a block update.

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void k_draw_indices(int32_t* __restrict__ idx,
     };
     start(mg.w0, mg.w, mg.K2, (int64_t)mg.G * mg.Hp, true);
     if (mg.v0) start(mg.v0, mg.v, mg.K2, (int64_t)mg.P * mg.Hp, false);
-    for (int64_t i = me; i < (int64_t)mg.K2 * mg.G * mg.Hp; i += step) mg.g[i] = 0;
+    for (int64_t i = me; i < mg.K2 * mg.g_block(); i += step) mg.g[i] = 0;
   }
   const uint64_t t0 = *step_ctr;
   const int64_t total = (int64_t)T * P * B;

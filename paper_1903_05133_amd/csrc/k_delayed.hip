@@ -556,7 +556,8 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   for (int i = tid; i < BM; i += NTH) {
     const int m = min(mrow0 + i, a.Mrows - 1);
     uint32_t e = 0;
-    for (int c = 0; c < a.gm_n; ++c) e = max(e, a.gmax[((int64_t)(g / a.gm_div) * a.gm_n + c) * a.Mrows + m]);
+#pragma unroll 4
+    for (int c = 0; c < a.gm_n; ++c) e = max(e, a.gmax[((int64_t)g * a.gm_n + c) * a.Mrows + m]);
     if (a.hb) {  // the errors carry their step's coefficient
       float f = 0.0f;
       for (int k = 0; k < a.K1; ++k) f = fmaxf(f, fabsf(a.hb[a.hb_g + k]));

@@ -206,3 +206,29 @@ def test_set_batch_into_the_delayed_schedule(c, B, gpu_lib):
         M.hieravg_round(prob, st)
         ok, det = cases.parity_report(prob, h.params(), st.W)
         assert ok, det
+
+
+@pytest.mark.parametrize("C", [5, 40])
+def test_buffers_of_learners_with_errors_of_any_magnitude(C, gpu_lib):
+    """One cluster whose second learner's W2, and with it its hidden errors, is
+    2^-36 of the first's: its own buffer of W1 keeps its relative accuracy (the
+    parity tolerance by learner; sums of at most 32 terms), whatever the
+    cluster's other errors are.  The step size leaves the parameters alone."""
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("mlp", 3, 3, 2, 1, B=16, IN=130, H=96, C=C, N=300, sigma=0.5, lr=1e-30, momentum=0.875, seed=216)
+    prob = cases.oracle_problem(c)
+    st = M.create(prob)
+    M.unpack(prob, st.W[1])["W2"][:] *= 2.0 ** -36
+    print(f"[gpu case] {c}", flush=True)
+    with HierAvg(config=cases.native_config(c, "delayed")) as h:
+        h.set_params(st.W.astype(np.float32))
+        h.profile(True)
+        h.round()
+        assert "buffer_update_gemm" in h.profile_read()
+        got = h.momentum()
+    M.hieravg_round(prob, st)
+    for p in range(prob.P):
+        g, w = M.unpack(prob, got[p].astype(np.float64))["W1"], M.unpack(prob, st.V[p])["W1"]
+        err = np.abs(g - w).max() / np.abs(w).max()
+        print("learner", p, "max", np.abs(w).max(), "error", err, flush=True)
+        assert err <= TOL, (p, err)
