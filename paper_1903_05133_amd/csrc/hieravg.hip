@@ -539,15 +539,11 @@ hipError_t measure_mags(hieravg* h) {
   const MagTables m = mag_tables(h);
   const size_t row = sizeof(uint32_t) * m.Hp;
   launch_row_maxima(h->stream, h->W + h->off_W1, 0, h->INp, h->INp, m.Hp, 1, m.w0);
-  for (int g = 0; g < m.G; ++g) {
-    const hipError_t e = hipMemcpyAsync(m.w + ((int64_t)(m.K2 - 1) * m.G + g) * m.Hp, m.w0, row,
-                                        hipMemcpyDeviceToDevice, h->stream);
-    if (e != hipSuccess) return e;
-  }
+  hipError_t e = hipMemcpyAsync(m.w + (int64_t)(m.K2 - 1) * m.G * m.Hp, m.w0, row, hipMemcpyDeviceToDevice, h->stream);
+  if (e != hipSuccess) return e;
   if (m.v0) {
     launch_row_maxima(h->stream, h->V + h->off_W1, h->Dp, h->INp, h->INp, m.Hp, m.P, m.v0);
-    const hipError_t e = hipMemcpyAsync(m.v + (int64_t)(m.K2 - 1) * m.P * m.Hp, m.v0, row * m.P,
-                                        hipMemcpyDeviceToDevice, h->stream);
+    e = hipMemcpyAsync(m.v + (int64_t)(m.K2 - 1) * m.P * m.Hp, m.v0, row * m.P, hipMemcpyDeviceToDevice, h->stream);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();
@@ -993,7 +989,8 @@ bool launch_class(hieravg* h, int kc, int tt) {
       a.gm_n = S / mg.gS;
       a.xexp = x_exp(h);
       a.hb_g = hb_index(HB_U, 0);
-      a.wmax_out = mg.w + (int64_t)b * mg.G * Hp;
+      // the last block's copies are only averaged: their mean takes its entries
+      if (b < c.K2 - 1 || h->global_last) a.wmax_out = mg.w + (int64_t)b * mg.G * Hp;
       if (b == c.K2 - 1 && h->global_last) {
         a.gm_n = P / mg.gS;
         // The last block: one update over all P learners from the mean of the
@@ -1025,9 +1022,13 @@ bool launch_class(hieravg* h, int kc, int tt) {
         launch_mean_rows(s, h->Wg, h->Wc, w1, w1, P / S, W + h->off_b1, h->Dp, h->Dp - h->off_b1, P);
         return true;
       }
-      launch_mean_rows(s, W + h->off_W1, wc_buf(h, c.K2 - 1), h->Hp * h->INp, h->Hp * h->INp, P / S,
-                       P > 1 ? W + h->off_b1 : nullptr,
-                       h->Dp, h->Dp - h->off_b1, P);
+      {
+        // The next round's scales are those of the mean itself, as a handle
+        // that resumes from it measures them.
+        const MagTables mg = mag_tables(h);
+        launch_mean_rows(s, W + h->off_W1, wc_buf(h, c.K2 - 1), w1, w1, P / S, P > 1 ? W + h->off_b1 : nullptr,
+                         h->Dp, h->Dp - h->off_b1, P, mg.w + (int64_t)(c.K2 - 1) * mg.G * Hp, INp);
+      }
       return true;
     case KC_GROUP_MEAN: launch_group_mean(s, W, h->Dp, h->Dp, P, S); return true;
     case KC_GLOBAL_MEAN: launch_group_mean(s, W, h->Dp, h->Dp, P, P); return true;

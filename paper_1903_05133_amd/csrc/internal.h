@@ -101,6 +101,18 @@ __device__ inline int xcd_remap(int bid, int nblocks) {
   return x * q + (x < r ? x : r) + i;
 }
 
+// The largest value of each 16 consecutive lanes, in all of them.
+template <int CTRL>
+__device__ inline uint32_t dpp_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+__device__ inline uint32_t max16(uint32_t m) {
+  m = max(m, dpp_u<0xB1>(m));  // lanes i^1, i^2, 7-i, 15-i
+  m = max(m, dpp_u<0x4E>(m));
+  m = max(m, dpp_u<0x141>(m));
+  return max(m, dpp_u<0x140>(m));
+}
+
 // ------------------------------------------------------------ kernel classes
 enum KernelClass {
   KC_DRAW = 0,       // minibatch index draw (once per round)
@@ -563,9 +575,12 @@ void launch_eval_rows(hipStream_t s, const float* part, int KS, int64_t split, c
 void launch_group_mean(hipStream_t s, float* W, int64_t pitch, int64_t len, int P, int S);
 // dst[i] = mean over r < n of src[r*pitch + i], i < len (multiples of 4
 // floats); in the same launch (W set) the columns [0, len_b) of the nb rows
-// of W (pitch_b apart) replaced by their mean.
+// of W (pitch_b apart) replaced by their mean.  wmax (optional): dst is a
+// matrix with rows of ld floats (a multiple of 64), whose entry of wmax is
+// raised to the row's largest magnitude.
 void launch_mean_rows(hipStream_t s, float* dst, const float* src, int64_t pitch, int64_t len, int n,
-                      float* W = nullptr, int64_t pitch_b = 0, int64_t len_b = 0, int nb = 0);
+                      float* W = nullptr, int64_t pitch_b = 0, int64_t len_b = 0, int nb = 0,
+                      uint32_t* wmax = nullptr, int64_t ld = 0);
 // flag = 1 if any of rows 1..n-1 of W (pitch floats apart) differs from row 0
 // in columns [0, len) (bit patterns; len a multiple of 4); flag untouched otherwise.
 void launch_rows_differ(hipStream_t s, const float* W, int64_t pitch, int64_t len, int n, int* flag);

@@ -73,21 +73,16 @@ __global__ __launch_bounds__(256) void k_draw_indices(int32_t* __restrict__ idx,
                                                       MagTables mg) {
   if (mg.w0) {
     const int64_t step = (int64_t)gridDim.x * 256, me = blockIdx.x * 256ll + threadIdx.x;
-    auto start = [&](uint32_t* dst, uint32_t* tab, int n, int64_t per, bool over) {
-      // dst = the last of the n entries of `per` values (over: the largest of
-      // its G rows), which is then cleared with the others
-      const int64_t len = over ? mg.Hp : per;
-      for (int64_t i = me; i < len; i += step) {
-        uint32_t m = 0;
-        for (int64_t o = i; o < per; o += len) {
-          m = max(m, tab[(n - 1) * per + o]);
-          for (int b = 0; b < n; ++b) tab[b * per + o] = 0;
-        }
-        dst[i] = m;
+    // dst = the first len of the last of n blocks of `per` entries, which are
+    // then cleared
+    auto start = [&](uint32_t* dst, uint32_t* tab, int n, int64_t per, int64_t len) {
+      for (int64_t i = me; i < per; i += step) {
+        if (i < len) dst[i] = tab[(n - 1) * per + i];
+        for (int b = 0; b < n; ++b) tab[b * per + i] = 0;
       }
     };
-    start(mg.w0, mg.w, mg.K2, (int64_t)mg.G * mg.Hp, true);
-    if (mg.v0) start(mg.v0, mg.v, mg.K2, (int64_t)mg.P * mg.Hp, false);
+    start(mg.w0, mg.w, mg.K2, (int64_t)mg.G * mg.Hp, mg.Hp);
+    if (mg.v0) start(mg.v0, mg.v, mg.K2, (int64_t)mg.P * mg.Hp, (int64_t)mg.P * mg.Hp);
     for (int64_t i = me; i < mg.K2 * mg.g_block(); i += step) mg.g[i] = 0;
   }
   const uint64_t t0 = *step_ctr;

@@ -434,11 +434,6 @@ void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
 }
 
 // ------------------------------------------------------------ block update
-template <int CTRL>
-__device__ inline uint32_t dpp_u(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-}
-
 // Wo_g = base_g - lr_eff * sum_r G[r][:]^T X[r][:] (BlkArgs), workgroup tile
 // BM units x BN inputs of one group's block, contracted over the group's
 // R = K1*SG*B rows 16 at a time.  A lane loads one or two columns of eight rows
@@ -657,11 +652,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
       uint32_t mine = 0;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        uint32_t m = mx[r];
-        m = max(m, dpp_u<0xB1>(m));  // lanes i^1, i^2, 7-i, 15-i
-        m = max(m, dpp_u<0x4E>(m));
-        m = max(m, dpp_u<0x141>(m));
-        m = max(m, dpp_u<0x140>(m));
+        const uint32_t m = max16(mx[r]);
         if ((lane & 15) == r) mine = m;
       }
       const int r = lane & 15;

@@ -232,3 +232,32 @@ def test_buffers_of_learners_with_errors_of_any_magnitude(C, gpu_lib):
         err = np.abs(g - w).max() / np.abs(w).max()
         print("learner", p, "max", np.abs(w).max(), "error", err, flush=True)
         assert err <= TOL, (p, err)
+
+
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_resume_is_exact_where_scales_lie_at_a_power_of_two(momentum, gpu_lib, tmp_path):
+    """Units whose largest weight is just below 1: in a cluster's copy it may
+    pass 1, in the mean of the copies not.  A running handle takes the next
+    round's scale (an exponent) from the mean, as a handle that resumes from
+    it does; the low bits of the other, tiny weights depend on it."""
+    from paper_1903_05133_amd import HierAvg
+    c = cases.case("mlp", 8, 2, 2, 2, B=32, IN=200, H=512, C=10, N=300, sigma=0.5, lr=0.05, momentum=momentum, seed=217)
+    cfg = cases.native_config(c, "delayed")
+    rng = np.random.default_rng(7)
+    print(f"[gpu case] {c}", flush=True)
+    with HierAvg(config=cfg) as h, HierAvg(config=cfg) as h2:
+        w = h.params()
+        W1 = (1e-7 * rng.standard_normal((c["H"], c["IN"]))).astype(np.float32)
+        W1[:, 0] = 1.0 - 1e-4 * rng.random(c["H"])
+        w[:, :W1.size] = W1.reshape(-1)
+        h.set_params(w)
+        for _ in range(4):
+            h.round()
+            h.save(str(tmp_path / "ck.npz"))
+            h.round()
+            h2.load(str(tmp_path / "ck.npz"))
+            h2.round()
+            assert np.array_equal(h2.params(), h.params())
+            w = h.params()  # back to the power of two
+            w[:, :W1.size] = W1.reshape(-1)
+            h.set_params(w)
