@@ -206,10 +206,12 @@ void launch_group_mean(hipStream_t s, float* W, int64_t pitch, int64_t len, int 
 
 // Workgroups below g1: dst = mean of the n rows of src.  The others (when W
 // is set): each column of the first n4b pieces of W's nb rows replaced by the
-// rows' mean, rows added in order.  MAX: dst has rows of ld4 pieces (a multiple
-// of 16, so that 16 consecutive lanes share a row) and the rows' largest
-// magnitudes go to wmax; only a value above what the table holds goes out.
-// (512 x 3072, four copies: 6.0 us, 5.5 without the maxima.)
+// rows' mean, rows added in order.  MAX: dst has rows of ld4 pieces, of which
+// a workgroup takes up to kMaxRun of one row, and the rows' largest magnitudes
+// go to wmax by an atomic per workgroup.  512 rows of 3072, four copies: 5.9
+// us, 5.6 without the maxima (two copies: 6.0 and 5.1); with an atomic per 16
+// lanes a round took 17 us more, with 256 pieces per workgroup the kernel 6.3.
+constexpr int kMaxRun = 1024;
 template <bool MAX>
 __global__ __launch_bounds__(256) void k_mean_rows(f32x4* __restrict__ dst, const f32x4* __restrict__ src,
                                                    int64_t pitch4, int64_t n4, int n, int g1, f32x4* __restrict__ W,
@@ -231,26 +233,26 @@ __global__ __launch_bounds__(256) void k_mean_rows(f32x4* __restrict__ dst, cons
     return sum;
   };
   if ((int)blockIdx.x < g1) {
-    const int64_t step = (int64_t)g1 * 256, i0 = blockIdx.x * 256ll + threadIdx.x;
-    int64_t row = MAX ? i0 / ld4 : 0, col = MAX ? i0 - row * ld4 : 0;
-    const int64_t srow = MAX ? step / ld4 : 0, scol = MAX ? step - srow * ld4 : 0;
-    for (int64_t i = i0; i < n4; i += step) {
-      const f32x4 mean = row_sum(src + i, pitch4, n) / (float)n;
-      dst[i] = mean;
-      if constexpr (MAX) {
-        uint32_t m = 0;  // magnitudes as bits: NaN and infinity are the largest
+    if constexpr (!MAX) {
+      for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n4; i += (int64_t)g1 * 256)
+        dst[i] = row_sum(src + i, pitch4, n) / (float)n;
+    } else {
+      __shared__ uint32_t part[4];
+      const int64_t runs = (ld4 + kMaxRun - 1) / kMaxRun, row = blockIdx.x / runs;
+      const int64_t c0 = (blockIdx.x - row * runs) * kMaxRun, c1 = min(ld4, c0 + kMaxRun);
+      uint32_t m = 0;  // magnitudes as bits: NaN and infinity are the largest
+      for (int64_t i = row * ld4 + c0 + threadIdx.x; i < row * ld4 + c1; i += 256) {
+        const f32x4 mean = row_sum(src + i, pitch4, n) / (float)n;
+        dst[i] = mean;
 #pragma unroll
         for (int e = 0; e < 4; ++e) m = max(m, __builtin_bit_cast(uint32_t, mean[e]) & 0x7fffffffu);
-        m = max16(m);
-        if ((threadIdx.x & 15) == 0 && m > __hip_atomic_load(wmax + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-          atomicMax(wmax + row, m);
-        row += srow;
-        col += scol;
-        if (col >= ld4) {
-          col -= ld4;
-          ++row;
-        }
       }
+      m = max16(m);
+      m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
+      m = max(m, (uint32_t)__shfl_xor((int)m, 32, 64));
+      if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+      __syncthreads();
+      if (threadIdx.x == 0) atomicMax(wmax + row, max(max(part[0], part[1]), max(part[2], part[3])));
     }
     return;
   }
@@ -264,7 +266,8 @@ __global__ __launch_bounds__(256) void k_mean_rows(f32x4* __restrict__ dst, cons
 void launch_mean_rows(hipStream_t s, float* dst, const float* src, int64_t pitch, int64_t len, int n, float* W,
                       int64_t pitch_b, int64_t len_b, int nb, uint32_t* wmax, int64_t ld) {
   const int64_t n4 = len / 4;
-  const unsigned g1 = col_runs(n4, 256, 1), gb = W ? col_runs(len_b / 4, 256, 1) : 0;
+  const unsigned g1 = wmax ? (unsigned)(len / ld * ((ld / 4 + kMaxRun - 1) / kMaxRun)) : col_runs(n4, 256, 1);
+  const unsigned gb = W ? col_runs(len_b / 4, 256, 1) : 0;
   auto go = [&](auto kernel) {
     launch(kernel, g1 + gb, 256, 0, s, (f32x4*)dst, (const f32x4*)src, pitch / 4, n4, n, (int)g1, (f32x4*)W,
            pitch_b / 4, len_b / 4, nb, wmax, ld / 4);
