@@ -365,8 +365,8 @@ int64_t plan(hieravg* h, int B) {
   const int64_t n1 = mlp ? h->Hp : h->Cp;
   h->Bp = (int)round_up(B, 16);
   h->KS2 = h->cps2 = 1;
-  plan_split(P, h->Bp, (int)n1, (int)h->INp, &h->KS1, &h->cps1);
-  if (mlp) plan_split(P, h->Bp, (int)h->Cp, (int)h->Hp, &h->KS2, &h->cps2);
+  plan_split(P, h->Bp, (int)n1, (int)h->INp, false, &h->KS1, &h->cps1);
+  if (mlp) plan_split(P, h->Bp, (int)h->Cp, (int)h->Hp, false, &h->KS2, &h->cps2);
   // The fused step kernels take the plain SGD step only.
   h->fused = h->T >= 2 && step_w1_supported(h->Bp, 1) && c.momentum == 0.0f && c.weight_decay == 0.0f;
   h->fused_mean = h->fused && c.S > 1 && step_w1_supported(h->Bp, c.S);
@@ -381,7 +381,7 @@ int64_t plan(hieravg* h, int B) {
                 c.weight_decay == 0.0f;
   h->head_fused = mlp && c.classes <= kSmallC && head_fused_supported((int)h->Hp, (int)round_up(c.classes, 16));
   if (h->upd_mean) {
-    plan_split(P / c.S, c.S * h->Bp, (int)n1, (int)h->INp, &h->KS_g, &h->cps_g);
+    plan_split(P / c.S, c.S * h->Bp, (int)n1, (int)h->INp, false, &h->KS_g, &h->cps_g);
     ks_max = std::max<int64_t>(ks_max, h->KS_g);
   }
   if (h->fused_mean) {
@@ -395,7 +395,7 @@ int64_t plan(hieravg* h, int B) {
   h->once_global = h->once_cond && h->once_alloc;
   h->once_block = h->once_global && h->upd_mean && c.S > 1;
   if (h->once_cond) {
-    plan_split(1, P * h->Bp, (int)h->Hp, (int)h->INp, &h->KS_g0, &h->cps_g0);
+    plan_split(1, P * h->Bp, (int)h->Hp, (int)h->INp, false, &h->KS_g0, &h->cps_g0);
     ks_max = std::max<int64_t>(ks_max, h->KS_g0);
   }
   h->delayed = false;
@@ -419,12 +419,12 @@ int64_t plan(hieravg* h, int B) {
                    !(h->hb && c.K2 < 2);
   if (h->delayed) {
     // One GEMM per cluster and block: the K1*S minibatches against the copy.
-    plan_split(P / c.S, c.K1 * c.S * h->Bp, (int)h->Hp, (int)h->INp, &h->KS_b, &h->cps_b);
+    plan_split(P / c.S, c.K1 * c.S * h->Bp, (int)h->Hp, (int)h->INp, true, &h->KS_b, &h->cps_b);
     ks_max = std::max<int64_t>(ks_max, (int64_t)h->KS_b * c.K1);
     // Heavy-ball with momentum: one more per learner, its K1 minibatches
     // against its own buffer.
     if (h->hb && c.momentum > 0.0f)
-      plan_split(P, c.K1 * h->Bp, (int)h->Hp, (int)h->INp, &h->KSv, &h->cpsv);
+      plan_split(P, c.K1 * h->Bp, (int)h->Hp, (int)h->INp, true, &h->KSv, &h->cpsv);
   }
   h->ks_cur = h->KS1;
   // What the last round ran, for hieravg_time_kernel, as far as this plan has
@@ -1588,7 +1588,7 @@ int eval_check(hieravg* h, int32_t replica, int32_t split, int64_t n_rows, const
 // Split count of a forward over one row group of Mp rows whose partials must
 // fit in `cap` floats (cap >= Mp * N).
 void split_within(int Mp, int N, int K, int64_t cap, int* KS, int* cps) {
-  plan_split(1, Mp, N, K, KS, cps);
+  plan_split(1, Mp, N, K, false, KS, cps);
   const int nch = K / 64;
   const int64_t ks_max = std::max<int64_t>(1, cap / ((int64_t)Mp * N));
   if (*KS > ks_max) {
@@ -1698,7 +1698,7 @@ int eval_scratch_plan(const hieravg* h, int* rows, int64_t* part_cap, int64_t* p
     int64_t p2 = 0;
     if (mlp) {
       int KS2, cps2;
-      plan_split(1, r, (int)h->Cp, (int)h->Hp, &KS2, &cps2);
+      plan_split(1, r, (int)h->Cp, (int)h->Hp, false, &KS2, &cps2);
       p2 = round_up((int64_t)KS2 * r * h->Cp, 64);
       if (fixed + p2 + r * n1 > kScratchFloats) p2 = round_up((int64_t)r * h->Cp, 64);
     }
@@ -1855,8 +1855,8 @@ int hieravg_evaluate(hieravg_t h, int32_t replica, int32_t split, int64_t n_rows
   // Partials for the split counts of a full chunk (a shorter last chunk
   // takes at most as many floats: split_within caps its splits).
   int ks1, ks2 = 1, cps;
-  plan_split(1, chunk, mlp ? Hp : Cp, INp, &ks1, &cps);
-  if (mlp) plan_split(1, chunk, Cp, Hp, &ks2, &cps);
+  plan_split(1, chunk, mlp ? Hp : Cp, INp, false, &ks1, &cps);
+  if (mlp) plan_split(1, chunk, Cp, Hp, false, &ks2, &cps);
   if (chunk > h->eval_rows) {
     void* old[] = {h->eval_iota, h->eval_part, h->eval_part2, h->eval_Z1, h->eval_loss, h->eval_hit};
     for (void* b : old)

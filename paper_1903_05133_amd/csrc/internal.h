@@ -282,8 +282,8 @@ struct FwdArgs {
 enum ASource { A_GATHER = 0, A_RELU = 1 };
 void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src);
 // Split count of a forward over `groups` row groups of GM rows each, no empty
-// split.
-void plan_split(int groups, int GM, int N, int K, int* KS, int* cps);
+// split; block: of a delayed block (vS > 0, two parts).
+void plan_split(int groups, int GM, int N, int K, bool block, int* KS, int* cps);
 // Outputs of 64 columns and more run as split products in 128- or 256-column
 // tiles (k_delayed.hip), narrower ones (the logits of few classes) as 16-column
 // float32 MFMA blocks (k_gemm.hip): there a wide tile is mostly padding (4 x 16

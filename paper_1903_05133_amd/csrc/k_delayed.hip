@@ -222,6 +222,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   constexpr int NTH = 64 * (BM / WM) * (BN / WN);
   constexpr int ROWS = BM + BN, RPP = NTH / 4, NP = (ROWS + RPP - 1) / RPP;  // pieces per thread, rows per pass
   constexpr int MI = WM / 32, NI = WN / 32;
+  constexpr bool DUAL = MI * NI <= 4;  // two sets of sums where the registers hold them
   using T = SplitTile<ROWS, NPART>;
   __shared__ __attribute__((aligned(16))) char lds[NTH == 512 ? 3 : 2][T::kBytes];
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
@@ -303,18 +304,13 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
       T::put4(tile, sr + RPP * i, sq, x);
     }
   };
-  f32x16 acc[MI][NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  SplitAcc<MI, NI, DUAL> acc;
+  acc.clear();
 
   if constexpr (NTH == 512)
-    split_loop8<ROWS, NPART, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
+    split_loop8<ROWS, NPART>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
   else
-    split_loop4<ROWS, NPART, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
+    split_loop4<ROWS, NPART>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
 
   int en[NI];  // two parts: minus the scales of the lane's columns
 #pragma unroll
@@ -340,18 +336,21 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
 #pragma unroll
         for (int e = 0; e < 4; ++e) 
           dst[(int64_t)e * a.N + 32 * j] =
-              NPART == 2 ? __builtin_amdgcn_ldexpf(acc[i][j][4 * t + e], en[j]) : acc[i][j][4 * t + e];
+              NPART == 2 ? __builtin_amdgcn_ldexpf(acc.sum[i][j][4 * t + e], en[j]) : acc.sum[i][j][4 * t + e];
       }
     }
   }
 }
 
 // The tile of a forward over `groups` row groups of GM rows each.
-//  - 256 x 256 where the operands are long: with the split count that brings
-//    the grid to one workgroup per CU, 1024 k and more per split (a 512-row
-//    group against 1024 units over 150528 features: 2.24 ms = 282 TFLOP/s, with
-//    128 x 256 tiles 2.47; over 3072 features the 128 x 256 tile is as fast
-//    with half the splits);
+//  - 256 x 256 for the forward of a delayed block where the operands are long:
+//    with the split count that brings the grid to one workgroup per CU, 1024 k
+//    and more per split (a 512-row group against 1024 units over 150528
+//    features: 2.24 ms = 282 TFLOP/s, with 128 x 256 tiles 2.47; over 3072
+//    features the 128 x 256 tile is as fast with half the splits).  Its
+//    registers hold one set of sums, which all three products round: still
+//    less than half as often as 32x32x2 float32 MFMAs, but not less than the
+//    16x16x4 ones of the other forwards, which therefore take the tiles below;
 //  - 128 x 256 where at least 32 such tiles exist, so that 8 splits fill the
 //    GPU (2048 rows, 512 units, 3072 features in two parts: 28.6 us, 31.8 us
 //    with 128 x 128 tiles; the float32 MFMA form took 66);
@@ -368,8 +367,8 @@ static constexpr FwdTileShape kFwdTiles[] = {{256, 256, 256}, {128, 256, 256}, {
 static int64_t fwd_tiles(FwdTile t, int64_t groups, int GM, int N) {
   return groups * ((GM + kFwdTiles[t].bm - 1) / kFwdTiles[t].bm) * ((N + kFwdTiles[t].bn - 1) / kFwdTiles[t].bn);
 }
-static FwdTile fwd_tile(int64_t groups, int GM, int N, int K) {
-  if (GM % 256 == 0 && N % 256 == 0) {
+static FwdTile fwd_tile(int64_t groups, int GM, int N, int K, bool block) {
+  if (block && GM % 256 == 0 && N % 256 == 0) {
     const int64_t ks = (256 + fwd_tiles(FT_256, groups, GM, N) - 1) / fwd_tiles(FT_256, groups, GM, N);
     if (K / ks >= 1024) return FT_256;
   }
@@ -377,13 +376,13 @@ static FwdTile fwd_tile(int64_t groups, int GM, int N, int K) {
   return GM > 32 ? FT_64 : FT_32;
 }
 
-void plan_split(int groups, int GM, int N, int K, int* KS, int* cps) {
+void plan_split(int groups, int GM, int N, int K, bool block, int* KS, int* cps) {
   const int nch = K / kKC;
   if (!fwd_split_takes(groups, GM, N, K)) {
     plan_split_nt(groups, GM, N, K, KS, cps);
     return;
   }
-  const FwdTile t = fwd_tile(groups, GM, N, K);
+  const FwdTile t = fwd_tile(groups, GM, N, K, block);
   const int64_t tiles = fwd_tiles(t, groups, GM, N);
   auto splits = [&](int64_t wgs) { return std::max<int64_t>(1, (wgs + tiles - 1) / tiles); };
   // Past 8 splits the partial sums cost more than two more workgroups per CU
@@ -422,8 +421,13 @@ void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
     else                                                                                                        \
       HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_GATHER, false);                                                    \
   } while (0)
-  switch (fwd_tile(groups, GM, a.N, a.K)) {
-    case FT_256: HAV_FS(256, 256, 128, 64, 2); break;
+  switch (fwd_tile(groups, GM, a.N, a.K, a.vS > 0)) {
+    case FT_256:
+      if (GM % 256 == 0 && a.N % 256 == 0 && a.M == a.Mp)
+        HAV_FS1(256, 256, 128, 64, 2, 2, A_GATHER, true);
+      else
+        HAV_FS1(256, 256, 128, 64, 2, 2, A_GATHER, false);
+      break;
     case FT_128x256: HAV_FS(128, 256, 64, 64, 2); break;
     case FT_128: HAV_FS(128, 128, 64, 32, 2); break;
     case FT_64: HAV_FS(64, 128, 64, 32, 4); break;
@@ -520,13 +524,8 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
     }
     load_tab(s + 1);
   };
-  f32x16 acc[MI][NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  SplitAcc<MI, NI, false> acc;
+  acc.clear();
 
   load_tab(0);
   const int voff = 4 * (4 * lhi * (int)a.ldw + l32), ld4 = 4 * (int)a.ldw;
@@ -584,9 +583,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   };
 
   if constexpr (NTH == 512)
-    split_loop8<ROWS, 2, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
+    split_loop8<ROWS, 2>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
   else
-    split_loop4<ROWS, 2, MI, NI>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
+    split_loop4<ROWS, 2>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
 
   // Straight from the accumulators: lane (l, h) holds column l of rows
   // 8t + 4h + e of each 32 x 32 block, so an instruction reads or writes two
@@ -621,7 +620,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int er = -a.xexp - gexp[wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3)];  // minus the scales
-        d[r] = c3 * __builtin_amdgcn_ldexpf(acc[i][j][r], er);
+        d[r] = c3 * __builtin_amdgcn_ldexpf(acc.sum[i][j][r], er);
       }
       if (a.hb && a.B2) {
         const float* b2 = a.B2 + (int64_t)g * a.b2_rows * a.b2_pitch;
@@ -754,12 +753,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
       T::put4(tile, sr + RPP * i, sq, x);
     }
   };
-  f32x16 acc[MI][1];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.0f;
-  split_loop8<ROWS, 2, MI, 1>(lds[0], ns, wm, kGB + wn, l32, lhi, wave >> 2, acc, load, store);
+  SplitAcc<MI, 1, false> acc;
+  acc.clear();
+  split_loop8<ROWS, 2>(lds[0], ns, wm, kGB + wn, l32, lhi, wave >> 2, acc, load, store);
   const int n = nt * kGB + wn + l32, k2 = n / Bp, s2 = n - k2 * Bp;
   float* out = gram + (((int64_t)ks * K2 + b) * P + p) * K1 * K1 * Bp * Bp;
 #pragma unroll
@@ -768,7 +764,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int r = 0; r < 16; ++r) {
       const int m = mt * kGB + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), k = m / Bp;
       if (m < R && n < R && k2 < k)
-        out[((int64_t)(k * K1 + k2) * Bp + (m - k * Bp)) * Bp + s2] = __builtin_amdgcn_ldexpf(acc[i][0][r], -2 * xexp);
+        out[((int64_t)(k * K1 + k2) * Bp + (m - k * Bp)) * Bp + s2] = __builtin_amdgcn_ldexpf(acc.sum[i][0][r], -2 * xexp);
     }
 }
 

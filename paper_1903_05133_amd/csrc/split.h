@@ -12,15 +12,20 @@
 // where that is more); three products are accumulated, and the one left out
 // is below 2^-22 of the product.
 //
-// Errors against float64 of dot products of 512 / 2048 / 18816 terms (relative
-// 2-norm): 4.0e-7 / 7.7e-7 / 2.4e-6 on the float32 MFMAs, 3.3e-7 / 6.9e-7 /
-// 2.4e-6 with three parts, 2.6e-7 / 5e-7 / 1.9e-6 with two: the rounding of
-// the accumulator dominates, and these MFMAs round it once per 16 terms and
-// product where the float32 one does once per 2 terms.  The matrix cores
-// sustain 145 TFLOP/s in float32 and 1850 in bf16 and f16 on random operands
-// (both limited by power), so six products take 0.47 of the time and three
-// 0.24; and vector instructions (the splitting) issue beside these MFMAs,
-// while they stall float32 ones.
+// The rounding of the float32 accumulators dominates the errors.  A product
+// of parts rounds its sum once per 16 terms, a float32 MFMA once per 4 (16x16x4)
+// or 2 (32x32x2).  Where all six products of three parts round one sum, runs
+// of 512 terms are 1.52 times as far from float64 as a float32 sum rounded
+// once per 4 terms; with the small products in a set of sums of their own
+// (SplitAcc) 0.59 times.  One sum for the three products of two parts rounds
+// less than half as often as the 32x32x2 form that it replaces (dot products
+// of 512 / 2048 / 18816 terms, relative 2-norm: 2.6e-7 / 5e-7 / 1.9e-6 against
+// 4.0e-7 / 7.7e-7 / 2.4e-6).
+//
+// The matrix cores sustain 145 TFLOP/s in float32 and 1850 in bf16 and f16 on
+// random operands, so six products take 0.47 of the time and three 0.24; and
+// vector instructions (the splitting) issue beside these MFMAs, while they
+// stall float32 ones.
 // An infinite operand gives NaN here (infinity times a zero part).
 #pragma once
 
@@ -121,10 +126,48 @@ struct SplitTile {
   }
 };
 
-// One stage (16 k) of a wave's MI x NI blocks of 32 x 32: rows ra + 32i of
-// the tile against rows rb + 32j.
-template <int ROWS, int NPART, int MI, int NI>
-__device__ inline void split_stage(const char* tile, int ra, int rb, int l32, int lhi, f32x16 (&acc)[MI][NI]) {
+// The float32 sums of a wave's MI x NI blocks of 32 x 32.  DUAL: the products
+// of the largest parts are summed by themselves, so that the full sum rounds
+// once per 16 terms, and the small ones (2^-8 of them and less) in a second
+// set, added at the end; without it every product rounds the one sum.
+template <int MI, int NI, bool DUAL>
+struct SplitAcc {
+  f32x16 sum[MI][NI];
+  f32x16 low[DUAL ? MI : 1][DUAL ? NI : 1];
+  __device__ void clear() {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[i][j][r] = 0.0f;
+          if constexpr (DUAL) low[i][j][r] = 0.0f;
+        }
+  }
+  // Adds product q (SplitOrder) of block (i, j); the last one is that of the
+  // largest parts.
+  template <int NPART>
+  __device__ void add(int q, int i, int j, u32x4 a, u32x4 b) {
+    if (DUAL && q < SplitOrder<NPART>::n - 1)
+      low[i][j] = mfma_part<NPART>(a, b, low[i][j]);
+    else
+      sum[i][j] = mfma_part<NPART>(a, b, sum[i][j]);
+  }
+  __device__ void finish() {
+    if constexpr (DUAL) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) sum[i][j] += low[i][j];
+    }
+  }
+};
+
+// One stage (16 k) of a wave's blocks: rows ra + 32i of the tile against rows
+// rb + 32j.
+template <int ROWS, int NPART, int MI, int NI, bool DUAL>
+__device__ inline void split_stage(const char* tile, int ra, int rb, int l32, int lhi, SplitAcc<MI, NI, DUAL>& acc) {
   using T = SplitTile<ROWS, NPART>;
   using O = SplitOrder<NPART>;
   u32x4 a[MI][NPART];
@@ -140,7 +183,7 @@ __device__ inline void split_stage(const char* tile, int ra, int rb, int l32, in
 #pragma unroll
     for (int q = 0; q < O::n; ++q)
 #pragma unroll
-      for (int i = 0; i < MI; ++i) acc[i][j] = mfma_part<NPART>(a[i][O::a[q]], b[O::b[q]], acc[i][j]);
+      for (int i = 0; i < MI; ++i) acc.template add<NPART>(q, i, j, a[i][O::a[q]], b[O::b[q]]);
   }
 }
 
@@ -148,8 +191,8 @@ __device__ inline void split_stage(const char* tile, int ra, int rb, int l32, in
 // barrier per stage, loads one stage ahead.  load(s): this thread's share of
 // stage s to registers (s past the end: anything in range), store(tile):
 // those registers to a tile.  ns is even.
-template <int ROWS, int NPART, int MI, int NI, class Load, class Store>
-__device__ inline void split_loop4(char* lds, int ns, int ra, int rb, int l32, int lhi, f32x16 (&acc)[MI][NI],
+template <int ROWS, int NPART, int MI, int NI, bool DUAL, class Load, class Store>
+__device__ inline void split_loop4(char* lds, int ns, int ra, int rb, int l32, int lhi, SplitAcc<MI, NI, DUAL>& acc,
                                    Load&& load, Store&& store) {
   using T = SplitTile<ROWS, NPART>;
   load(0);
@@ -160,23 +203,24 @@ __device__ inline void split_loop4(char* lds, int ns, int ra, int rb, int l32, i
     store(lds + T::kBytes);
     load(s + 2);
     __builtin_amdgcn_sched_barrier(0);
-    split_stage<ROWS, NPART, MI, NI>(lds, ra, rb, l32, lhi, acc);
+    split_stage<ROWS, NPART>(lds, ra, rb, l32, lhi, acc);
     __syncthreads();
     store(lds);
     load(s + 3);
     __builtin_amdgcn_sched_barrier(0);
-    split_stage<ROWS, NPART, MI, NI>(lds + T::kBytes, ra, rb, l32, lhi, acc);
+    split_stage<ROWS, NPART>(lds + T::kBytes, ra, rb, l32, lhi, acc);
     __syncthreads();
   }
+  acc.finish();
 }
 
 // The contraction of a workgroup of eight waves, waves 0-3 and 4-7 (one of
 // each per SIMD) half a stage apart: while four waves read their operands of
 // a stage from LDS, the other four run the MFMAs of theirs, and split and
 // write (store) the stage two ahead beside them.  Three stage buffers at lds.
-template <int ROWS, int NPART, int MI, int NI, class Load, class Store>
+template <int ROWS, int NPART, int MI, int NI, bool DUAL, class Load, class Store>
 __device__ inline void split_loop8(char* lds, int ns, int ra, int rb, int l32, int lhi, int grp,
-                                   f32x16 (&acc)[MI][NI], Load&& load, Store&& store) {
+                                   SplitAcc<MI, NI, DUAL>& acc, Load&& load, Store&& store) {
   using T = SplitTile<ROWS, NPART>;
   using O = SplitOrder<NPART>;
   load(0);
@@ -207,7 +251,7 @@ __device__ inline void split_loop8(char* lds, int ns, int ra, int rb, int l32, i
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int i = 0; i < MI; ++i) acc[i][j] = mfma_part<NPART>(fa[i][O::a[q]], fb[j][O::b[q]], acc[i][j]);
+        for (int i = 0; i < MI; ++i) acc.template add<NPART>(q, i, j, fa[i][O::a[q]], fb[j][O::b[q]]);
     store(lds + nxt);
     load(s + 3);
 #pragma unroll
@@ -223,6 +267,7 @@ __device__ inline void split_loop8(char* lds, int ns, int ra, int rb, int l32, i
     nxt = nxt == 2 * T::kBytes ? 0 : nxt + T::kBytes;
   }
   if (!grp) __builtin_amdgcn_s_barrier();
+  acc.finish();
 }
 
 }  // namespace hav

@@ -261,3 +261,38 @@ def test_resume_is_exact_where_scales_lie_at_a_power_of_two(momentum, gpu_lib, t
             w = h.params()  # back to the power of two
             w[:, :W1.size] = W1.reshape(-1)
             h.set_params(w)
+
+
+@pytest.mark.parametrize("P,B,C", [(1024, 32, 64), (512, 48, 64), (256, 80, 64), (256, 80, 192)],
+                         ids=["32", "64", "128", "128x256"])
+def test_three_part_forward_is_as_exact_as_a_float32_sum(P, B, C, gpu_lib):
+    """Logits z_c = v x + e_c x whose large common share v x (about 1000) drops
+    out of the softmax but sets the rounding of every logit, so that one step's
+    bias gradient shows the logits' error, far above its own rounding.  It is at
+    most that of a float32 sum that rounds once per four terms (the 16x16x4
+    matrix instruction), computed here; with all six products rounding one sum
+    it is above.  As many learners as leave one split of the features, so that
+    both sum 512 terms in one run; forward tiles of 32, 64 and 128 rows."""
+    from paper_1903_05133_amd import HierAvg
+    from oracle import rng as R
+    c = cases.case("softmax", P, 1, 1, 1, B=B, IN=512, C=C, N=400, sigma=0.5, lr=1e-30, momentum=0.5, seed=218)
+    gen = np.random.default_rng(3)
+    W = (gen.standard_normal((C, c["IN"])) + 1000.0 * gen.standard_normal(c["IN"])) / np.sqrt(c["IN"])
+    W = W.astype(np.float32)
+    row = np.concatenate([W.reshape(-1), np.zeros(C, np.float32)])
+    print(f"[gpu case] {c}", flush=True)
+    with HierAvg(config=cases.native_config(c)) as h:
+        h.set_params(np.broadcast_to(row, (P, row.size)).copy())
+        h.round()
+        got = h.momentum()[:, -C:].astype(np.float64)
+        idx = h.last_indices().reshape(P, B).astype(np.int64)
+    X, y = R.data_rows(c["seed"], np.arange(c["N"]), c["IN"], C, c["sigma"])
+    terms = [X[:, k:k + 4] @ W[:, k:k + 4].T.astype(np.float64) for k in range(0, c["IN"], 4)]
+    z4 = np.zeros((c["N"], C), np.float32)
+    for t in terms:
+        z4 = (z4.astype(np.float64) + t).astype(np.float32)
+    grad = lambda z: (M.softmax_probs(z) - np.eye(C)[y])[idx].mean(axis=1)  # noqa: E731
+    want = grad(sum(terms))
+    err, err4 = (np.sqrt(np.mean((g - want) ** 2)) for g in (got, grad(z4.astype(np.float64))))
+    print("error", err, "of a float32 sum", err4, "ratio", err / err4, flush=True)
+    assert err <= err4, (err, err4)
