@@ -83,12 +83,12 @@ def parity_report(prob, got, want):
         err = {n: np.abs(g[n] - w[n]) / max(float(np.max(np.abs(w[n]))), 1e-30) for n in w}
         if prob.kind == M.MLP:
             unit_err = np.maximum.reduce([err["W1"].max(axis=1), err["b1"], err["W2"].max(axis=0)])
-            units |= set(np.nonzero(unit_err > TOL)[0].tolist())
+            units |= set(np.nonzero(~(unit_err <= TOL))[0].tolist())
         for n, e in err.items():
             m = float(e.max()) if e.size else 0.0
-            if m > details["worst"][1]:
+            if m > details["worst"][1] or np.isnan(m):
                 details["worst"] = ((p, n), m)
-            if m > TOL:
+            if not m <= TOL:  # (NaN fails)
                 ok = False
                 details.setdefault("fail", []).append((p, n, m))
     details["units"] = sorted(units)
