@@ -249,23 +249,25 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   const float* wp = a.W + (int64_t)(g / a.wdiv) * a.w_pitch;
   const uint32_t* wmax = NPART == 2 ? a.wmax + (int64_t)(g / a.wdiv) * a.wmax_pitch : nullptr;
   const float inv_mp = qdiv_inv(a.Mp), inv_vs = qdiv_inv(a.vS > 0 ? a.vS : 1);
+  // Row m of the group's A; past its samples (not valid: zeros) row 0's.
+  auto a_row = [&](int m, bool& valid) {
+    const int jj = qdiv_small(m, a.Mp, inv_mp), sm = m - jj * a.Mp;
+    valid = FULL || (m < GM && sm < a.M);
+    const int v = valid ? jj : 0;
+    int64_t p = (int64_t)g * a.SG + v;
+    if (a.vS > 0) {
+      const int k = qdiv_small(v, a.vS, inv_vs);
+      p = (int64_t)k * a.P + (int64_t)g * a.vS + (v - k * a.vS);
+    }
+    const int sc = valid ? sm : 0;
+    return a.A + (ASRC == A_GATHER ? (int64_t)a.idx[p * a.M + sc] : p * a.Mp + sc) * a.lda;
+  };
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     if (none(i)) continue;
     const int r = sr + RPP * i;
     if (is_a(i)) {
-      const int m = mbase + r;
-      const int jj = qdiv_small(m, a.Mp, inv_mp), sm = m - jj * a.Mp;
-      ok[i] = FULL || (m < GM && sm < a.M);
-      const int v = ok[i] ? jj : 0;
-      int64_t p = (int64_t)g * a.SG + v;
-      if (a.vS > 0) {
-        const int k = qdiv_small(v, a.vS, inv_vs);
-        p = (int64_t)k * a.P + (int64_t)g * a.vS + (v - k * a.vS);
-      }
-      const int sc = ok[i] ? sm : 0;
-      const int64_t row = ASRC == A_GATHER ? (int64_t)a.idx[p * a.M + sc] : p * a.Mp + sc;
-      src[i] = a.A + row * a.lda + 4 * sq;
+      src[i] = a_row(mbase + r, ok[i]) + 4 * sq;
       ex[i] = a.xexp;
     } else {
       const int n = nbase + r - BM;
@@ -311,6 +313,75 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
     split_loop8<ROWS, NPART>(lds[0], ns, wm, BM + wn, l32, lhi, wave >> 2, acc, load, store);
   else
     split_loop4<ROWS, NPART>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
+
+  // Infinite operands: one of their parts is NaN, and so is every sum that they
+  // enter.  Those sums are taken again here, as float32 gives them.
+  auto nan = [](float x) { return x != x; };
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    if constexpr (ASRC == A_GATHER) {
+      // Dataset rows are finite, so every row of the column has a NaN, and only
+      // the column's infinite weights count (with a NaN weight it is right as it
+      // is): the wave looks for them together, then takes one row of either half
+      // at a time.
+      for (uint32_t cols = __builtin_amdgcn_readfirstlane((uint32_t)__ballot(nan(acc.sum[0][j][0]))); cols;
+           cols &= cols - 1) {
+        const int col = __builtin_ctz(cols), n = min(nbase + wn + 32 * j + col, a.N - 1);
+        const float* w = wp + (int64_t)n * a.ldw;
+        bool inf = false, nans = false;
+        for (int k = c0 * kKC; k < c1 * kKC && !nans; k += 64) {
+          const float v = w[k + lane];
+          nans = __any(nan(v));
+          inf = inf || __any(__builtin_isinf(v));
+        }
+        if (nans || !inf) continue;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          for (int q = 0; q < 16; ++q) {
+            bool valid;
+            const float* x = a_row(mbase + wm + 32 * i + 8 * (q >> 2) + 4 * lhi + (q & 3), valid);
+            float s = 0.0f;
+            bool all = false;  // NaN in both halves
+            for (int k = c0 * kKC; k < c1 * kKC && !all; k += 64)
+              for (uint64_t b = __ballot(__builtin_isinf(w[k + lane])); b && !all; b &= b - 1) {
+                const int kk = k + __builtin_ctzll(b);
+                s = __builtin_fmaf(valid ? x[kk] : 0.0f, w[kk], s);
+                all = __all(nan(s));
+              }
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              if (r == q && l32 == col) acc.sum[i][j][r] = s;
+          }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        f32x16& sum = acc.sum[i][j];
+        float t = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t += sum[r];
+        if (!nan(t)) continue;
+        const float* w = wp + (int64_t)min(nbase + wn + 32 * j + l32, a.N - 1) * a.ldw;
+        float s[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+        bool all = false;
+        for (int k = c0 * kKC; k < c1 * kKC && !all; ++k) {
+          all = true;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            bool valid;
+            const float* x = a_row(mbase + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), valid);
+            s[r] = __builtin_fmaf(!valid || x[k] < 0.0f ? 0.0f : x[k], w[k], s[r]);
+            all = all && nan(s[r]);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (nan(sum[r])) sum[r] = s[r];
+      }
+    }
+  }
 
   int en[NI];  // two parts: minus the scales of the lane's columns
 #pragma unroll
@@ -587,6 +658,45 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   else
     split_loop4<ROWS, 2>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
 
+  // Units with infinite errors: as in the forward, from those errors alone (the
+  // dataset rows are finite).
+  auto nan = [](float x) { return x != x; };
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if (!__any(gexp[wm + 32 * i + l32] == kNonFiniteExp)) continue;
+    for (int u = 0; u < 32; ++u) {
+      const int m = mrow0 + wm + 32 * i + u;
+      if (gexp[wm + 32 * i + u] != kNonFiniteExp || m >= a.Mrows) continue;
+      auto err = [&](int r) { return r < R ? a.G[((uint64_t)gt[r] << 6) + m] : 0.0f; };
+      bool inf = false, nans = false;
+      for (int r = 0; r < R && !nans; r += 64) {
+        const float e = err(r + lane);
+        nans = __any(nan(e));
+        inf = inf || __any(__builtin_isinf(e));
+      }
+      if (nans || !inf) continue;
+      float s[NI];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) s[j] = 0.0f;
+      bool all = false;
+      for (int r0 = 0; r0 < R && !all; r0 += 64)
+        for (uint64_t b = __ballot(__builtin_isinf(err(r0 + lane))); b && !all; b &= b - 1) {
+          const int r = r0 + __builtin_ctzll(b);
+          all = true;
+#pragma unroll
+          for (int j = 0; j < NI; ++j) {
+            const int n = min(ncol0 + wn + 32 * j + l32, a.Ncols - 1);
+            s[j] = __builtin_fmaf(err(r), a.X[((uint64_t)xt[r] << 6) + n], s[j]);
+            all = all && __all(nan(s[j]));
+          }
+        }
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (8 * (r >> 2) + 4 * lhi + (r & 3) == u) acc.sum[i][j][r] = s[j];
+    }
+  }
   // Straight from the accumulators: lane (l, h) holds column l of rows
   // 8t + 4h + e of each 32 x 32 block, so an instruction reads or writes two
   // 128-byte row segments.  Buffer accesses: one lane offset for the whole

@@ -26,7 +26,8 @@
 // random operands, so six products take 0.47 of the time and three 0.24; and
 // vector instructions (the splitting) issue beside these MFMAs, while they
 // stall float32 ones.
-// An infinite operand gives NaN here (infinity times a zero part).
+// An infinite operand gives NaN here (one of its parts is NaN, and infinity
+// times a zero part): the kernels take such sums again in float32.
 #pragma once
 
 #include "internal.h"
@@ -44,6 +45,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Exponent e such that a magnitude m (the bits of a nonnegative float) scaled
 // by 2^e lies in [2^14, 2^15) (below it for subnormals and zero).
 __host__ __device__ inline int split_exp(uint32_t bits) { return 141 - (int)(bits >> 23); }
+constexpr int kNonFiniteExp = 141 - 255;  // of an infinite or NaN magnitude
 
 // The NPART parts of two floats, each part's pair packed (low half: a).
 template <int NPART>

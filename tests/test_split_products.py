@@ -296,3 +296,83 @@ def test_three_part_forward_is_as_exact_as_a_float32_sum(P, B, C, gpu_lib):
     err, err4 = (np.sqrt(np.mean((g - want) ** 2)) for g in (got, grad(z4.astype(np.float64))))
     print("error", err, "of a float32 sum", err4, "ratio", err / err4, flush=True)
     assert err <= err4, (err, err4)
+
+
+# (update mode, minibatch, hidden units, classes): the forward's forms and tiles
+@pytest.mark.parametrize("mode,B,H,C", [("delayed", 16, 96, 5), ("delayed", 16, 300, 40), ("auto", 48, 512, 5),
+                                        ("eager", 16, 96, 5), ("eager", 48, 96, 40), ("eager", 80, 300, 70)])
+def test_an_infinite_weight_acts_as_in_float32(mode, B, H, C, gpu_lib):
+    """A weight of -infinity at a feature that is positive in every row (five
+    rows without noise: class means): the unit's pre-activations are -infinity,
+    it is off for good, and every other parameter takes the steps of the oracle's
+    run with a huge weight there."""
+    from paper_1903_05133_amd import HierAvg
+    from oracle import rng as R
+    c = cases.case("mlp", 4, 2, 2, 2, B=B, IN=1100, H=H, C=C, N=5, sigma=0.0, lr=0.01, seed=219)
+    X, _ = R.data_rows(c["seed"], np.arange(c["N"]), c["IN"], C, 0.0)
+    prob = cases.oracle_problem(c)
+    st = M.create(prob)
+    k = 7 * c["IN"] + int(np.flatnonzero((X > 0.01).all(axis=0))[-1])
+    st.W[:, k] = -np.inf
+    print(f"[gpu case] infinite weight {mode} {c}", flush=True)
+    with HierAvg(config=cases.native_config(c, mode)) as h:
+        h.set_params(st.W.astype(np.float32))
+        h.round()
+        got = h.params()
+    st.W[:, k] = -1e30  # as good as infinite (the oracle's 0 * weight of no decay is finite)
+    M.hieravg_round(prob, st)
+    assert (got[:, k] == -np.inf).all() and (np.isinf(got).sum(axis=1) == 1).all()
+    got[:, k] = st.W[:, k] = 0.0
+    ok, det = cases.parity_report(prob, got, st.W)
+    assert ok, det
+
+
+@pytest.mark.parametrize("rows", [64, 1500, 2100])
+def test_evaluate_with_an_infinite_weight(rows, gpu_lib):
+    """One weight of -infinity: its unit is off in the rows that are positive
+    there, and in the others its logits are infinite, the first positively
+    infinite one being the prediction."""
+    from paper_1903_05133_amd import HierAvg
+    from oracle import rng as R
+    c = cases.case("mlp", 1, 1, 1, 1, B=16, IN=300, H=520, C=70, N=2100, sigma=0.5, lr=0.05, seed=220)
+    prob = cases.oracle_problem(c)
+    w = M.create(prob).W.astype(np.float32)
+    w[0, 7 * c["IN"] + 3] = -np.inf
+    X, y = R.data_rows(c["seed"], np.arange(rows), c["IN"], c["C"], c["sigma"])
+    b = M.unpack(prob, w[0].astype(np.float64))
+    z = np.maximum(X @ b["W1"].T + b["b1"], 0.0) @ b["W2"].T + b["b2"]
+    assert not np.isnan(z).any() and np.isinf(z).any(axis=1).sum() > rows / 4
+    print(f"[gpu case] infinite weight, evaluate {rows}", flush=True)
+    with HierAvg(config=cases.native_config(c)) as h:
+        h.set_params(w)
+        _, correct = h.evaluate(0, 0, rows)
+    assert abs(correct - int((z.argmax(axis=1) == y).sum())) <= 1  # (a near-tie of finite logits)
+
+
+@pytest.mark.parametrize("momentum", [0.0, 0.5])
+def test_an_infinite_error_acts_as_in_float32(momentum, gpu_lib):
+    """One learner, one sample, one step: a unit just above zero whose weights
+    of 3e38 in W2 make its error overflow to infinity; its row of W1 (and of
+    its buffer) takes the infinities of error times input."""
+    from paper_1903_05133_amd import HierAvg
+    from oracle import rng as R
+    c = cases.case("mlp", 1, 1, 1, 1, B=1, IN=64, H=64, C=2, N=9, sigma=0.5, lr=0.5, momentum=momentum, seed=221)
+    prob = cases.oracle_problem(c)
+    row = int(R.draw_indices(c["seed"], 0, 0, 1, c["N"])[0])
+    X, y = R.data_rows(c["seed"], np.array([row]), c["IN"], c["C"], c["sigma"])
+    w = M.create(prob).W.astype(np.float32)
+    b = M.unpack(prob, w[0])
+    b["W1"][7] = 0.0
+    b["b1"][7] = 1e-30
+    b["W2"][:, 7] = 3e38
+    b["W2"][y[0], 7] = -3e38  # the label's logit is the lowest: error 3e38 + 3e38
+    print(f"[gpu case] infinite error {c}", flush=True)
+    with HierAvg(config=cases.native_config(c, "delayed")) as h:
+        h.set_params(w)
+        h.round()
+        got = M.unpack(prob, h.params()[0])["W1"]
+        buf = M.unpack(prob, h.momentum()[0])["W1"] if momentum else None
+    want = np.where(X[0] > 0, -np.inf, np.inf)
+    assert np.array_equal(got[7], want) and np.isfinite(np.delete(got, 7, axis=0)).all()
+    if momentum:
+        assert np.array_equal(buf[7], -want)
