@@ -354,14 +354,17 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
           }
       }
     } else {
+      // Hidden values may be infinite too: every term again, lane by lane (row m
+      // of a group is row m of its block; vS = 0).
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         f32x16& sum = acc.sum[i][j];
         float t = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) t += sum[r];
-        if (!nan(t)) continue;
+        if (!__any(nan(t))) continue;
         const float* w = wp + (int64_t)min(nbase + wn + 32 * j + l32, a.N - 1) * a.ldw;
+        const float* x = a.A + (int64_t)g * GM * a.lda;
         float s[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.0f;
@@ -370,9 +373,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
           all = true;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            bool valid;
-            const float* x = a_row(mbase + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), valid);
-            s[r] = __builtin_fmaf(!valid || x[k] < 0.0f ? 0.0f : x[k], w[k], s[r]);
+            const int m = min(mbase + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), GM - 1);
+            const float v = x[(int64_t)m * a.lda + k];
+            s[r] = __builtin_fmaf(v < 0.0f ? 0.0f : v, w[k], s[r]);
             all = all && nan(s[r]);
           }
         }
@@ -501,7 +504,7 @@ void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
       break;
     case FT_128x256: HAV_FS(128, 256, 64, 64, 2); break;
     case FT_128: HAV_FS(128, 128, 64, 32, 2); break;
-    case FT_64: HAV_FS(64, 128, 64, 32, 4); break;
+    case FT_64: HAV_FS(64, 128, 64, 32, 3); break;
     default: HAV_FS(32, 128, 32, 32, 4); break;
   }
 #undef HAV_FS
