@@ -485,12 +485,15 @@ PlanNeed plan_need(hieravg* h, int B) {
 }
 
 // What every minibatch size up to Bmax needs (hieravg_set_batch may take any).
-// Every size is planned: the schedule depends on B itself (K1 * S * B rows at
-// most), so a size may be delayed, with its rows padded to 16, where the next
-// multiple of 16 is not.
+// A plan depends on the size padded to 16, but for one limit: the delayed
+// schedule takes up to kBlkMaxRows rows K1 * S * B of the size itself, so the
+// largest size within it may be delayed where the next multiple of 16 is not.
 PlanNeed plan_need_upto(hieravg* h, int Bmax) {
   PlanNeed m;
-  for (int b = 1; b <= Bmax; ++b) {
+  const int64_t rows_max = kBlkMaxRows / std::max<int64_t>(1, (int64_t)h->cfg.K1 * h->cfg.S);
+  std::vector<int> sizes = {Bmax, (int)std::min<int64_t>(Bmax, std::max<int64_t>(1, rows_max))};
+  for (int b = 16; b < Bmax; b += 16) sizes.push_back(b);
+  for (int b : sizes) {
     const PlanNeed n = plan_need(h, b);
     m.part = std::max(m.part, n.part);
     m.part2 = std::max(m.part2, n.part2);
