@@ -214,15 +214,18 @@ void launch_gram_reduce(hipStream_t s, float* gram, int P, int K1, int K2, int B
 // Workgroup tile BM rows (samples) x BN columns (units), one K split; wave
 // tile WM x WN.  The tile's rows of both operands are read 16 k at a time
 // with 16-byte loads (four lanes per row), one stage ahead in registers, and
-// go to LDS as bf16 parts (two buffers, one barrier per stage).  FULL: every
-// row and column in range.
-template <int BM, int BN, int WM, int WN, int NPART, int ASRC, bool FULL, int WPE>
+// go to LDS as three bf16 or two f16 parts (the loops of split.h).  FULL: every
+// row and column in range.  DUAL: a second set of sums for the small products
+// (SplitAcc): in every form but the two parts of a delayed block, which replaced
+// 32x32x2 float32 MFMAs and round less than half as often with one set; there
+// the registers of a second one leave the 128 x 256 tile one workgroup per CU
+// (288 workgroups, 16 x 320 rows, 448 units, 1104 features: 33 -> 42 us).
+template <int BM, int BN, int WM, int WN, int NPART, int ASRC, bool FULL, bool DUAL, int WPE>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_waves_per_eu(WPE))) void k_fwd_split(
     FwdArgs a, int ntiles, int mtiles) {
   constexpr int NTH = 64 * (BM / WM) * (BN / WN);
   constexpr int ROWS = BM + BN, RPP = NTH / 4, NP = (ROWS + RPP - 1) / RPP;  // pieces per thread, rows per pass
   constexpr int MI = WM / 32, NI = WN / 32;
-  constexpr bool DUAL = MI * NI <= 4;  // two sets of sums where the registers hold them
   using T = SplitTile<ROWS, NPART>;
   __shared__ __attribute__((aligned(16))) char lds[NTH == 512 ? 3 : 2][T::kBytes];
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
@@ -421,10 +424,8 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
 //    with the split count that brings the grid to one workgroup per CU, 1024 k
 //    and more per split (a 512-row group against 1024 units over 150528
 //    features: 2.24 ms = 282 TFLOP/s, with 128 x 256 tiles 2.47; over 3072
-//    features the 128 x 256 tile is as fast with half the splits).  Its
-//    registers hold one set of sums, which all three products round: still
-//    less than half as often as 32x32x2 float32 MFMAs, but not less than the
-//    16x16x4 ones of the other forwards, which therefore take the tiles below;
+//    features the 128 x 256 tile is as fast with half the splits); the other
+//    forwards take two sets of sums, which this tile's registers do not hold;
 //  - 128 x 256 where at least 32 such tiles exist, so that 8 splits fill the
 //    GPU (2048 rows, 512 units, 3072 features in two parts: 28.6 us, 31.8 us
 //    with 128 x 128 tiles; the float32 MFMA form took 66);
@@ -458,7 +459,12 @@ void plan_split(int groups, int GM, int N, int K, bool block, int* KS, int* cps)
   }
   const FwdTile t = fwd_tile(groups, GM, N, K, block);
   const int64_t tiles = fwd_tiles(t, groups, GM, N);
-  auto splits = [&](int64_t wgs) { return std::max<int64_t>(1, (wgs + tiles - 1) / tiles); };
+  // With two sets of sums one workgroup of the 128 x 256 tile fits a CU, and two
+  // of the 128 x 128 one slow each other: no more than one per CU, then (3327
+  // rows, 448 units, 2816 features, twice: 194 us with 208 workgroups, 254 with
+  // 260; 3002 rows, 128 units, 7104 features: 177 with 240, 194 with 264).
+  const bool at_most = !block && (t == FT_128x256 || t == FT_128);
+  auto splits = [&](int64_t wgs) { return std::max<int64_t>(1, (at_most ? wgs : wgs + tiles - 1) / tiles); };
   // Past 8 splits the partial sums cost more than two more workgroups per CU
   // give (softmax, 8 learners, 7776 features, 97 classes: 2.41 ms a job with one
   // split per 64 features, 1.85 with one per 128).
@@ -477,36 +483,36 @@ void launch_fwd(hipStream_t s, const FwdArgs& a, ASource src) {
     launch_fwd_nt(s, a, src);
     return;
   }
-#define HAV_FS1(BM_, BN_, WM_, WN_, WPE_, NPART_, SRC_, FULL_)                                                  \
-  launch(k_fwd_split<BM_, BN_, WM_, WN_, NPART_, SRC_, FULL_, WPE_>,                                            \
+#define HAV_FS1(BM_, BN_, WM_, WN_, WPE_, NPART_, SRC_, FULL_, DUAL_)                                           \
+  launch(k_fwd_split<BM_, BN_, WM_, WN_, NPART_, SRC_, FULL_, DUAL_, WPE_>,                                     \
          (unsigned)((int64_t)groups * a.KS * ((GM + BM_ - 1) / BM_) * ((a.N + BN_ - 1) / BN_)),                 \
          64 * (BM_ / WM_) * (BN_ / WN_), 0, s, a, (a.N + BN_ - 1) / BN_, (GM + BM_ - 1) / BM_)
+#define HAV_FS2(BM_, BN_, WM_, WN_, WPE_, NPART_, DUAL_)                                                        \
+  do {                                                                                                          \
+    if (GM % BM_ == 0 && a.N % BN_ == 0 && a.M == a.Mp)                                                         \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, NPART_, A_GATHER, true, DUAL_);                                         \
+    else                                                                                                        \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, NPART_, A_GATHER, false, DUAL_);                                        \
+  } while (0)
 #define HAV_FS(BM_, BN_, WM_, WN_, WPE_)                                                                        \
   do {                                                                                                          \
-    const bool full = GM % BM_ == 0 && a.N % BN_ == 0 && a.M == a.Mp;                                           \
     if (src == A_RELU)                                                                                          \
-      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_RELU, false);                                                      \
-    else if (a.wmax && full)                                                                                    \
-      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 2, A_GATHER, true);                                                     \
-    else if (a.wmax)                                                                                            \
-      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 2, A_GATHER, false);                                                    \
-    else if (full)                                                                                              \
-      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_GATHER, true);                                                     \
+      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_RELU, false, true);                                                \
+    else if (!a.wmax)                                                                                           \
+      HAV_FS2(BM_, BN_, WM_, WN_, WPE_, 3, true);                                                               \
+    else if (a.vS > 0)                                                                                          \
+      HAV_FS2(BM_, BN_, WM_, WN_, WPE_, 2, false);                                                              \
     else                                                                                                        \
-      HAV_FS1(BM_, BN_, WM_, WN_, WPE_, 3, A_GATHER, false);                                                    \
+      HAV_FS2(BM_, BN_, WM_, WN_, WPE_, 2, true);                                                               \
   } while (0)
   switch (fwd_tile(groups, GM, a.N, a.K, a.vS > 0)) {
-    case FT_256:
-      if (GM % 256 == 0 && a.N % 256 == 0 && a.M == a.Mp)
-        HAV_FS1(256, 256, 128, 64, 2, 2, A_GATHER, true);
-      else
-        HAV_FS1(256, 256, 128, 64, 2, 2, A_GATHER, false);
-      break;
+    case FT_256: HAV_FS2(256, 256, 128, 64, 2, 2, false); break;
     case FT_128x256: HAV_FS(128, 256, 64, 64, 2); break;
     case FT_128: HAV_FS(128, 128, 64, 32, 2); break;
     case FT_64: HAV_FS(64, 128, 64, 32, 3); break;
     default: HAV_FS(32, 128, 32, 32, 4); break;
   }
+#undef HAV_FS2
 #undef HAV_FS
 #undef HAV_FS1
 }
