@@ -253,7 +253,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   const uint32_t* wmax = NPART == 2 ? a.wmax + (int64_t)(g / a.wdiv) * a.wmax_pitch : nullptr;
   const float inv_mp = qdiv_inv(a.Mp), inv_vs = qdiv_inv(a.vS > 0 ? a.vS : 1);
   // Row m of the group's A; past its samples (not valid: zeros) row 0's.
-  auto a_row = [&](int m, bool& valid) {
+  auto a_row = [&](int m, bool& valid, float inv_mp, float inv_vs) {
     const int jj = qdiv_small(m, a.Mp, inv_mp), sm = m - jj * a.Mp;
     valid = FULL || (m < GM && sm < a.M);
     const int v = valid ? jj : 0;
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
     if (none(i)) continue;
     const int r = sr + RPP * i;
     if (is_a(i)) {
-      src[i] = a_row(mbase + r, ok[i]) + 4 * sq;
+      src[i] = a_row(mbase + r, ok[i], inv_mp, inv_vs) + 4 * sq;
       ex[i] = a.xexp;
     } else {
       const int n = nbase + r - BM;
@@ -318,73 +318,24 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
     split_loop4<ROWS, NPART>(lds[0], ns, wm, BM + wn, l32, lhi, acc, load, store);
 
   // Infinite operands: one of their parts is NaN, and so is every sum that they
-  // enter.  Those sums are taken again here, as float32 gives them.
+  // enter.  Which sums those are is noted here, and they are taken again, as
+  // float32 gives them, after the others are stored (their code and registers
+  // stay out of the way).
   auto nan = [](float x) { return x != x; };
+  uint32_t cols[NI];  // gathered rows: columns with a NaN; hidden ones: blocks i with a NaN
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
+    cols[j] = 0;
     if constexpr (ASRC == A_GATHER) {
-      // Dataset rows are finite, so every row of the column has a NaN, and only
-      // the column's infinite weights count (with a NaN weight it is right as it
-      // is): the wave looks for them together, then takes one row of either half
-      // at a time.
-      for (uint32_t cols = __builtin_amdgcn_readfirstlane((uint32_t)__ballot(nan(acc.sum[0][j][0]))); cols;
-           cols &= cols - 1) {
-        const int col = __builtin_ctz(cols), n = min(nbase + wn + 32 * j + col, a.N - 1);
-        const float* w = wp + (int64_t)n * a.ldw;
-        bool inf = false, nans = false;
-        for (int k = c0 * kKC; k < c1 * kKC && !nans; k += 64) {
-          const float v = w[k + lane];
-          nans = __any(nan(v));
-          inf = inf || __any(__builtin_isinf(v));
-        }
-        if (nans || !inf) continue;
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-          for (int q = 0; q < 16; ++q) {
-            bool valid;
-            const float* x = a_row(mbase + wm + 32 * i + 8 * (q >> 2) + 4 * lhi + (q & 3), valid);
-            float s = 0.0f;
-            bool all = false;  // NaN in both halves
-            for (int k = c0 * kKC; k < c1 * kKC && !all; k += 64)
-              for (uint64_t b = __ballot(__builtin_isinf(w[k + lane])); b && !all; b &= b - 1) {
-                const int kk = k + __builtin_ctzll(b);
-                s = __builtin_fmaf(valid ? x[kk] : 0.0f, w[kk], s);
-                all = __all(nan(s));
-              }
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (r == q && l32 == col) acc.sum[i][j][r] = s;
-          }
-      }
+      // dataset rows are finite: a column's weights make NaN of every row
+      cols[j] = __builtin_amdgcn_readfirstlane((uint32_t)__ballot(nan(acc.sum[0][j][0])));
     } else {
-      // Hidden values may be infinite too: every term again, lane by lane (row m
-      // of a group is row m of its block; vS = 0).
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        f32x16& sum = acc.sum[i][j];
         float t = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) t += sum[r];
-        if (!__any(nan(t))) continue;
-        const float* w = wp + (int64_t)min(nbase + wn + 32 * j + l32, a.N - 1) * a.ldw;
-        const float* x = a.A + (int64_t)g * GM * a.lda;
-        float s[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-        bool all = false;
-        for (int k = c0 * kKC; k < c1 * kKC && !all; ++k) {
-          all = true;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int m = min(mbase + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), GM - 1);
-            const float v = x[(int64_t)m * a.lda + k];
-            s[r] = __builtin_fmaf(v < 0.0f ? 0.0f : v, w[k], s[r]);
-            all = all && nan(s[r]);
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (nan(sum[r])) sum[r] = s[r];
+        for (int r = 0; r < 16; ++r) t += acc.sum[i][j][r];
+        cols[j] |= __any(nan(t)) ? 1u << i : 0u;
       }
     }
   }
@@ -396,6 +347,15 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
   const int64_t PT = a.PT > 0 ? a.PT : a.P;
   const int64_t gbase = a.vS > 0 ? (int64_t)g * a.vS : (int64_t)g * a.SG;
   const int64_t kstride = a.vS > 0 ? a.P : 0;
+  // (computed again: the loop's registers are at the limit of their occupancy)
+  int mp2 = a.Mp, vs2 = a.vS > 0 ? a.vS : 1;
+  asm volatile("" : "+s"(mp2), "+s"(vs2));
+  const float inv_mp2 = qdiv_inv(mp2), inv_vs2 = qdiv_inv(vs2);
+  auto out = [&](int row) {  // row of the group -> its partial sums
+    const int mv = qdiv_small(row, a.Mp, inv_mp2), sm = row - mv * a.Mp;
+    const int vk = a.vS > 0 ? qdiv_small(mv, a.vS, inv_vs2) : 0, vj = a.vS > 0 ? mv - vk * a.vS : mv;
+    return a.part + (((int64_t)ks * PT + vk * kstride + gbase + vj) * a.Mp + sm) * a.N;
+  };
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     // The lane's rows 8t + e (e < 4) share one member (Mp is a multiple of 16).
@@ -404,16 +364,65 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) __attribute__((amdgpu_w
     for (int t = 0; t < 4; ++t) {
       const int row = mrow + 8 * t;
       if (!FULL && row >= GM) continue;
-      const int mv = qdiv_small(row, a.Mp, inv_mp), sm = row - mv * a.Mp;
-      const int vk = a.vS > 0 ? qdiv_small(mv, a.vS, inv_vs) : 0, vj = a.vS > 0 ? mv - vk * a.vS : mv;
-      float* dst = a.part + (((int64_t)ks * PT + vk * kstride + gbase + vj) * a.Mp + sm) * a.N + nbase + wn + l32;
+      float* dst = out(row) + nbase + wn + l32;
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
         if (!FULL && nbase + wn + 32 * j + l32 >= a.N) continue;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) 
+        for (int e = 0; e < 4; ++e)
           dst[(int64_t)e * a.N + 32 * j] =
               NPART == 2 ? __builtin_amdgcn_ldexpf(acc.sum[i][j][4 * t + e], en[j]) : acc.sum[i][j][4 * t + e];
+      }
+    }
+  }
+
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    if (__builtin_expect(cols[j] == 0, 1)) continue;
+    if constexpr (ASRC == A_GATHER) {
+      // Only the column's infinite weights count (with a NaN weight the sums are
+      // right as they are): the wave looks for them together, then takes one row
+      // of either half at a time.
+      for (uint32_t left = cols[j]; left; left &= left - 1) {
+        const int col = nbase + wn + 32 * j + __builtin_ctz(left);
+        if (col >= a.N) break;
+        const float* w = wp + (int64_t)col * a.ldw;
+        bool inf = false, nans = false;
+        for (int k = c0 * kKC; k < c1 * kKC && !nans; k += 64) {
+          const float v = w[k + l32 + 32 * lhi];
+          nans = __any(nan(v));
+          inf = inf || __any(__builtin_isinf(v));
+        }
+        if (nans || !inf) continue;
+        for (int q = 0; q < 16 * MI; ++q) {
+          const int row = mbase + wm + 8 * (q >> 2) + 4 * lhi + (q & 3);
+          bool valid;
+          const float* x = a_row(row, valid, inv_mp2, inv_vs2);
+          float s = 0.0f;
+          bool all = false;  // NaN in both halves
+          for (int k = c0 * kKC; k < c1 * kKC && !all; k += 64)
+            for (uint64_t b = __ballot(__builtin_isinf(w[k + l32 + 32 * lhi])); b && !all; b &= b - 1) {
+              const int kk = k + __builtin_ctzll(b);
+              s = __builtin_fmaf(valid ? x[kk] : 0.0f, w[kk], s);
+              all = __all(nan(s));
+            }
+          if (l32 == __builtin_ctz(left) && (FULL || row < GM)) out(row)[col] = s;
+        }
+      }
+    } else {
+      // Hidden values may be infinite too: every term again, lane by lane (row m
+      // of a group is row m of its block; vS = 0).  A finite sum had no infinite
+      // operand and stays.
+      const int col = nbase + wn + 32 * j + l32;
+      const float* w = wp + (int64_t)min(col, a.N - 1) * a.ldw;
+      for (int q = 0; q < 16 * MI; ++q) {
+        if (!(cols[j] >> (q >> 4) & 1)) continue;
+        const int row = mbase + wm + 8 * (q >> 2) + 4 * lhi + (q & 3);
+        const float* x = a.A + ((int64_t)g * GM + min(row, GM - 1)) * a.lda;
+        float s = 0.0f;
+        for (int k = c0 * kKC; k < c1 * kKC && !nan(s); ++k)
+          s = __builtin_fmaf(x[k] < 0.0f ? 0.0f : x[k], w[k], s);
+        if (!__builtin_isfinite(s) && row < GM && col < a.N) out(row)[col] = s;
       }
     }
   }
