@@ -523,10 +523,9 @@ def test_delayed_schedule_profile(gpu_lib):
 
 
 def test_delayed_block_update_large_grid(gpu_lib):
-    """Cluster updates with at least eight full 128 x 128 tiles per CU (8
-    clusters x 4 x 64 tiles: the two-chain block-update tile) and the tail
-    means of b1, W2, b2 in the same launch: P=16 S=2 K1=4 K2=2 B=32, a
-    8192-512-10 MLP, two rounds against the oracle."""
+    """Cluster updates with two whole 256 x 256 tiles per CU (8 clusters x 2 x
+    32) and the tail means of b1, W2, b2 in the same launch: P=16 S=2 K1=4
+    K2=2 B=32, a 8192-512-10 MLP, two rounds against the oracle."""
     c = cases.case("mlp", 16, 2, 4, 2, B=32, IN=8192, H=512, C=10, N=300, sigma=0.5, lr=0.02, seed=44)
     got, idx, _ = _run_gpu(c, rounds=2, mode="delayed")
     _check(c, got, idx, *_oracle(c, 2), mode="delayed")
@@ -534,10 +533,9 @@ def test_delayed_block_update_large_grid(gpu_lib):
 
 def test_delayed_block_forward_many_clusters(gpu_lib):
     """Block forwards of 8 clusters x 4 steps x 32 samples (1024 rows per
-    cluster, 2048 inputs, 512 hidden units): with the split count that fills
-    the GPU, 256 x 256 tiles would keep splits under 64 chunks, so the launch
-    takes the 128 x 128 tile with one split over all 2048 inputs, the plan made
-    for that tile.  P=64 S=8 K1=4 K2=1 B=32, one round against the oracle."""
+    cluster, 2048 inputs, 512 hidden units): with the split count that brings
+    them to one per CU, 256 x 256 tiles would contract 512 inputs each, so the
+    launch takes the 128 x 256 tile and the split count of that tile.  P=64 S=8 K1=4 K2=1 B=32, one round against the oracle."""
     c = cases.case("mlp", 64, 8, 4, 1, B=32, IN=2048, H=512, C=10, N=2000, sigma=0.5, lr=0.05, seed=45)
     got, idx, _ = _run_gpu(c, rounds=1, mode="delayed")
     _check(c, got, idx, *_oracle(c, 1), mode="delayed")

@@ -1,6 +1,7 @@
 """The wide contractions as split float32 products (csrc/split.h,
 csrc/k_delayed.hip): every tile of the forward and of the block update at its
-edges, and operands of very different magnitudes, against the CPU oracle.
+edges, whole and ragged, and operands of very different magnitudes, against
+the CPU oracle.
 
 Tolerance: the 1e-4 gate of the parity tests for whole parameter blocks.  For
 the magnitudes test the same 1e-4 holds for every hidden unit by itself:
@@ -14,7 +15,7 @@ import pytest
 
 import cases
 from oracle import method as M
-from test_gpu_parity import TOL, _check, _oracle, _run_gpu
+from test_gpu_parity import TOL, _check, _momentum_run, _oracle, _run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +41,13 @@ TILES = {
     # 1024 features)
     "delayed_256": (cases.case("mlp", 32, 2, 8, 1, B=16, IN=4096, H=1024, C=5, N=300, sigma=0.5, lr=0.05, seed=207),
                     "delayed"),
+    # the same tiles with minibatches that do not fill their padded rows
+    "delayed_256_ragged": (cases.case("mlp", 32, 2, 8, 1, B=13, IN=4096, H=1024, C=5, N=300, sigma=0.5, lr=0.05, seed=227),
+                           "delayed"),
+    # 256 x 256 block-update tiles, ragged in features (16 clusters of 256 rows,
+    # 512 units, 4160 features: 17 column tiles, the last of 64)
+    "delayed_update_256": (cases.case("mlp", 32, 2, 4, 2, B=32, IN=4150, H=500, C=5, N=300, sigma=0.5, lr=0.05, seed=228),
+                           "delayed"),
     # 128 x 128 block-update tiles, ragged (320 units, 3008 features)
     "delayed_update_128": (cases.case("mlp", 16, 4, 2, 2, B=9, IN=3001, H=310, C=5, N=300, sigma=0.5, lr=0.05, seed=208),
                            "delayed"),
@@ -59,9 +67,28 @@ TILES = {
 @pytest.mark.parametrize("name", sorted(TILES))
 def test_tiles_match_oracle(name, gpu_lib):
     c, mode = TILES[name]
-    rounds = 1 if name == "delayed_256" else 2
+    rounds = 1 if "256" in name else 2
     got, idx, _ = _run_gpu(c, rounds, mode)
     _check(c, got, idx, *_oracle(c, rounds), mode=mode)
+
+
+@pytest.mark.parametrize("P,S,K1,K2,B,IN,H", [(32, 2, 4, 2, 32, 4150, 500), (32, 2, 4, 2, 32, 4096, 512),
+                                              (16, 4, 2, 2, 9, 3001, 310), (4, 2, 2, 2, 7, 130, 70)],
+                         ids=["256_ragged", "256", "128", "64"])
+def test_heavy_ball_block_update_tiles(P, S, K1, K2, B, IN, H, gpu_lib):
+    """The block update's tiles with buffers: parameters and every learner's
+    buffers against the oracle (its run with the decisions at rounding that the
+    kernels took)."""
+    c = cases.case("mlp", P, S, K1, K2, B=B, IN=IN, H=H, C=5, N=300, sigma=0.5, lr=0.01, momentum=0.9,
+                   weight_decay=1e-3, seed=229)
+    got, vgot, idx, stats = _momentum_run(c, "delayed", rounds=1)
+    assert "buffer_update_gemm" in stats
+    st, mon, rerun = _oracle(c, 1)
+    _check(c, got, idx, st, mon, rerun, mode="delayed")
+    # A decision that the mean of the parameters hides moves its own learner's buffer.
+    prob = cases.oracle_problem(c)
+    ok, det = cases.branch_parity(prob, vgot, st.V, mon, lambda flips: M.run(prob, 1, flips=flips).V)
+    assert ok, det
 
 
 @pytest.mark.parametrize("name", [n for n in sorted(TILES) if n.startswith("wide")])
@@ -110,12 +137,13 @@ def test_units_of_any_magnitude(mode, momentum, gpu_lib):
     with HierAvg(config=cases.native_config(c, mode)) as h:
         h.set_params(st.W.astype(np.float32))
         h.round()
-        got = h.params()
+        got = [h.params()] + ([h.momentum()] if momentum else [])
     M.hieravg_round(prob, st)
-    for p in range(prob.P):
-        g, w = M.unpack(prob, got[p].astype(np.float64)), M.unpack(prob, st.W[p])
-        err = np.abs(g["W1"] - w["W1"]).max(axis=1) / np.abs(w["W1"]).max(axis=1)
-        assert err.max() <= TOL, (int(err.argmax()), float(err.max()))
+    for arr, want in zip(got, (st.W, st.V)):  # every unit's parameters, and its row of every learner's buffer
+        for p in range(prob.P):
+            g, w = M.unpack(prob, arr[p].astype(np.float64)), M.unpack(prob, want[p])
+            err, size = np.abs(g["W1"] - w["W1"]).max(axis=1), np.abs(w["W1"]).max(axis=1)
+            assert (err <= TOL * size).all(), np.flatnonzero(~(err <= TOL * size))
 
 
 @pytest.mark.parametrize("value", [np.inf, np.nan])
@@ -133,12 +161,12 @@ def test_non_finite_weights_stay_visible(value, gpu_lib):
         assert not h.finite()
 
 
-@pytest.mark.parametrize("rows", [2032, 2033, 4096, 4097])
-def test_evaluate_around_the_measured_form(rows, gpu_lib):
-    """Chunks of 2048 padded rows and more take W1's rows as two parts; ragged
-    widths, rows of W1 of very different magnitudes."""
+@pytest.mark.parametrize("rows,H", [(2032, 100), (2033, 100), (4096, 100), (4097, 100), (4096, 512), (4090, 300)])
+def test_evaluate_around_the_measured_form(rows, H, gpu_lib):
+    """Chunks of 2048 padded rows and more take W1's rows as two parts, in 128-
+    or 256-column tiles; ragged widths, rows of W1 of very different magnitudes."""
     from paper_1903_05133_amd import HierAvg
-    c = cases.case("mlp", 2, 1, 1, 1, B=16, IN=101, H=100, C=7, N=4200, sigma=0.5, lr=0.05, seed=231)
+    c = cases.case("mlp", 2, 1, 1, 1, B=16, IN=101, H=H, C=7, N=4200, sigma=0.5, lr=0.05, seed=231)
     prob = cases.oracle_problem(c)
     st = M.create(prob)
     scale = 10.0 ** np.linspace(-6, 6, prob.H)
