@@ -78,8 +78,8 @@ typedef struct hieravg* hieravg_t;
  *  AUTO:    DELAYED where it applies and its extra Gram products cost at most
  *           an eighth of the step's flops ((K1 - 1) * B <= H / 2); also, with
  *           plain SGD, for 32 < B <= 128 where (K1 - 1) * B <= H and W1 holds
- *           2^19 floats or more (B, H, W1 padded to 16, 64, 64 x 64); else
- *           EAGER.
+ *           2^19 floats or more (B, H, W1 padded to 16, 64, 64 x 64) and its
+ *           buffers fit in memory; else EAGER.
  */
 #define HIERAVG_UPDATE_AUTO 0
 #define HIERAVG_UPDATE_EAGER 1

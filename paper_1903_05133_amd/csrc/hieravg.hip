@@ -139,6 +139,7 @@ struct hieravg {
   bool delayed = false;    // the handle uses them for rounds that start with equal W1
   bool global_last = false; // the last block's update takes the global mean (K1*P*B rows fit)
   bool wide = false;        // delayed updates with minibatches of 33 to 128 samples (AUTO only)
+  bool any_wide = false, no_wide = false;  // some minibatch takes them; none may (no memory for their buffers)
   bool hb = false;          // delayed updates with momentum or weight decay (heavy-ball blocks)
   int KSv = 1, cpsv = 1;    // splits of the block-wide forward from the learners' buffers
   float* partv = nullptr;   // [KSv][K1][P][Bp][Hp] partials of X_k V^T (momentum > 0)
@@ -405,7 +406,8 @@ int64_t plan(hieravg* h, int B) {
     const bool cheap = (int64_t)(c.K1 - 1) * h->Bp * 2 <= h->Hp;
     h->delayed = c.update_mode == HIERAVG_UPDATE_DELAYED || (c.update_mode == HIERAVG_UPDATE_AUTO && cheap);
   }
-  h->wide = mlp && !h->delayed && c.update_mode == HIERAVG_UPDATE_AUTO && wide_applies(h, B);
+  h->wide = mlp && !h->delayed && !h->no_wide && c.update_mode == HIERAVG_UPDATE_AUTO && wide_applies(h, B);
+  h->any_wide = h->any_wide || h->wide;
   h->delayed = h->delayed || h->wide;
   h->KSG = !h->delayed ? 1 : h->wide ? gram_split_splits(P, c.K1, c.K2, h->Bp, (int)h->INp)
                                      : gram_splits(P, c.K2, (int)h->INp);
@@ -1400,24 +1402,36 @@ hieravg_t hieravg_create_config(const hieravg_config* cfg) {
     return nullptr;
   }
   if (validate(*cfg) != HIERAVG_OK) return nullptr;
-  hieravg* h = new (std::nothrow) hieravg;
-  if (!h) {
-    set_error("out of host memory");
-    return nullptr;
-  }
-  h->cfg = *cfg;
-  h->fail_alloc = forced_alloc_failure();
-  // Steps per round; K2 becomes the number of blocks (the last one shorter
-  // when K1 does not divide k_global).
-  h->T = cfg->k_global > 0 ? cfg->k_global : cfg->K1 * cfg->K2;
-  h->cfg.k_global = h->T;
-  h->cfg.K2 = (h->T + cfg->K1 - 1) / cfg->K1;
-  if (build(h) != HIERAVG_OK) {
-    std::string msg = g_last_error;
+  hieravg* h = nullptr;
+  int n_allocs = 0;
+  for (bool no_wide : {false, true}) {
+    h = new (std::nothrow) hieravg;
+    if (!h) {
+      set_error("out of host memory");
+      return nullptr;
+    }
+    h->cfg = *cfg;
+    h->no_wide = no_wide;
+    h->n_allocs = n_allocs;
+    h->fail_alloc = forced_alloc_failure();
+    // Steps per round; K2 becomes the number of blocks (the last one shorter
+    // when K1 does not divide k_global).
+    h->T = cfg->k_global > 0 ? cfg->k_global : cfg->K1 * cfg->K2;
+    h->cfg.k_global = h->T;
+    h->cfg.K2 = (h->T + cfg->K1 - 1) / cfg->K1;
+    if (build(h) == HIERAVG_OK) break;
+    // Without the memory for the delayed schedule of more than 32 samples, which
+    // AUTO may leave out: eager rounds.
+    const bool again = h->any_wide;
+    n_allocs = h->n_allocs;
+    const std::string msg = g_last_error;
     release(h);
+    (void)hipGetLastError();
     set_error(msg);
-    return nullptr;
+    h = nullptr;
+    if (!again) return nullptr;
   }
+  if (!h) return nullptr;
   g_last_error.clear();
   return h;
 }

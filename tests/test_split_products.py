@@ -404,3 +404,37 @@ def test_an_infinite_error_acts_as_in_float32(momentum, gpu_lib):
     assert np.array_equal(got[7], want) and np.isfinite(np.delete(got, 7, axis=0)).all()
     if momentum:
         assert np.array_equal(buf[7], -want)
+
+
+def test_no_memory_for_the_wide_schedule_leaves_eager_rounds(gpu_lib, monkeypatch):
+    """AUTO with 64 samples: an allocation that fails (by the debug hook) leaves a
+    handle of eager rounds, whose smaller minibatches stay delayed."""
+    from dataclasses import replace
+    from paper_1903_05133_amd import HierAvg
+    c, _ = TILES["wide_64"]
+    n = 2  # (the first one comes before the schedule is known: the create fails)
+    print(f"[gpu case] no memory {c}", flush=True)
+    while True:  # allocations of a whole create
+        monkeypatch.setenv("HIERAVG_FAIL_ALLOC", str(n))
+        with HierAvg(config=cases.native_config(c)) as h:
+            h.profile(True)
+            h.round()
+            if "fwd1_block_gemm" in h.profile_read():
+                break
+        n += 1
+    assert n > 10
+    for fail in (2, n - 10, n - 1):
+        monkeypatch.setenv("HIERAVG_FAIL_ALLOC", str(fail))
+        prob = cases.oracle_problem(c)
+        st = M.create(prob)
+        with HierAvg(config=cases.native_config(c)) as h:
+            for B, delayed in ((64, False), (20, True)):
+                prob = replace(prob, B=B)
+                h.set_batch(B)
+                h.profile(True)
+                h.round()
+                assert ("fwd1_block_gemm" in h.profile_read()) == delayed
+                h.profile(False)
+                M.hieravg_round(prob, st)
+                ok, det = cases.parity_report(prob, h.params(), st.W)
+                assert ok, det
