@@ -299,10 +299,10 @@ int hieravg_kernel_classes(void);
  * Mean duration in milliseconds of one launch of kernel class
  * `kernel_class` (see hieravg_kernel_class_name), from HIP events around one
  * launch of a graph of `reps` back-to-back launches of it (captured on the
- * handle's stream) with the arguments of step 0 of the current round.  For measurement only: the launches act on the replicas as
- * `reps` extra applications of that kernel would.  HIERAVG_EINVAL for a class
- * the workload does not launch, for the index draw, or while profiling.
- * Synchronises.
+ * handle's stream) with the arguments of step 0 of the current round.  For
+ * measurement only: the launches act on the replicas as `reps` extra
+ * applications of that kernel would.  HIERAVG_EINVAL for a class the workload
+ * does not launch, for the index draw, or while profiling.  Synchronises.
  */
 int hieravg_time_kernel(hieravg_t h, int kernel_class, int reps, double* mean_ms);
 const char* hieravg_kernel_class_name(int c);

@@ -337,13 +337,14 @@ int validate(const hieravg_config& c) {
 
 // Minibatches of 33 to 128 samples under AUTO (plain SGD): the delayed schedule
 // with the head kernels of the eager one, the Gram blocks as a split product
-// and the correction as a kernel of its own.  Where the Gram work stays below
+// and the correction as a kernel of its own, where the Gram work stays below
 // about half of the step's ((K1 - 1) * B <= H) and W1 is large enough for its
-// traffic to count: an eager step reads and writes every learner's W1, or, past
-// the fused step (B > 64), runs it through an update and a forward.  Figures
-// of a round, eager and delayed: 64 learners of 3072-512-10, 8 x 64 samples a
-// block: 8.8 ms and 4.3; 8 learners of 3072-512-100, 4 x 128: 1.18 ms (1.53 before the split
-// products) and 0.81.
+// traffic to count.  Both lines are on the safe side: the schedule is ahead on
+// both sides of them.  A round of 16 learners, S = 4, K2 = 2, 10 classes, eager
+// and delayed, in us: 64 samples, K1 = 4, 2^19 floats of W1 (1024 x 512) 400 and
+// 308, 2^18 (512 x 512, taken eager) 324 and 287, 768 x 256 286 and 269; 128
+// samples, 3072 x 512, K1 = 5 (4 * 128 = H) 1311 and 867, K1 = 8 (taken eager)
+// 2046 and 1511; 64 samples, 3072 x 256, K1 = 8 (taken eager) 918 and 688.
 bool wide_applies(const hieravg* h, int B) {
   const hieravg_config& c = h->cfg;
   const int64_t Bp = round_up(B, 16);
@@ -411,11 +412,14 @@ int64_t plan(hieravg* h, int B) {
   h->delayed = h->delayed || h->wide;
   h->KSG = !h->delayed ? 1 : h->wide ? gram_split_splits(P, c.K1, c.K2, h->Bp, (int)h->INp)
                                      : gram_splits(P, c.K2, (int)h->INp);
-  // The last block's update over all P learners has one group of output
-  // tiles (64 x 128); with fewer than two per CU the G cluster updates and a
-  // separate mean of the copies fill the GPU better.  Heavy-ball blocks with
-  // one block per round keep the cluster updates: the buffers' update needs
-  // the block-start parameters, which the global update would overwrite.
+  // The last block's update over all P learners is one group of tiles; below
+  // W1 of 2^22 floats (256 tiles of 128 x 128, one per CU) the G cluster updates
+  // and a separate mean of the copies fill the GPU better.  A round of K1 = 4,
+  // K2 = 2, 32 samples, 512 units, one update and copies, in us: 2^20 floats
+  // 256 and 214 (16 learners, S = 4), 273 and 231 (S = 1); 2^22 432 and 404, 568
+  // and 582; 2^23 699 and 707, 950 and 1103.  Heavy-ball blocks with one block
+  // per round keep the cluster updates: the buffers' update needs the block-start
+  // parameters, which the global update would overwrite.
   h->hb = h->delayed && (c.momentum > 0.0f || c.weight_decay > 0.0f);
   h->global_last = h->delayed && (int64_t)c.K1 * P * B <= kBlkMaxRows && (h->Hp / 64) * (h->INp / 128) >= 512 &&
                    !(h->hb && c.K2 < 2);
