@@ -199,11 +199,24 @@ def source_record(path, workload, kernel_class):
 
 
 def mfma_peak(kernel, c):
-    """Matrix peak for float32 products as this kernel class takes them."""
+    """Matrix peak for float32 products as this kernel class takes them: two
+    f16 parts in the delayed schedule, three bf16 parts in the other forwards
+    of 64 padded columns and more unless few rows meet weights that stream from
+    HBM (fwd_split_takes in csrc/internal.h), else float32."""
     if kernel in SPLIT2_CLASSES or (kernel == "gram" and c["B"] > 32):
         return SPLIT2_PEAK_TFLOPS
-    wide = {"fwd1_gemm": c["H"] or c["C"], "fwd1_group_gemm": c["H"], "fwd2_gemm": c["C"]}
-    return SPLIT3_PEAK_TFLOPS if wide.get(kernel, 0) >= 64 else FP32_MFMA_PEAK_TFLOPS
+    import cases
+    pad = lambda n, m: (n + m - 1) // m * m  # noqa: E731
+    P, S, Bp, INp, Hp, Cp = c["P"], c["S"], pad(c["B"], 16), pad(c["IN"], 64), pad(c["H"], 64), pad(c["C"], 16)
+    first = (P, Bp, Hp or Cp, INp)  # row groups, rows of each, columns, contraction
+    if c["kind"] == "mlp" and cases.eager_means_once(c)[0]:
+        first = (1, P * Bp, Hp, INp)
+    forms = {"fwd1_gemm": first, "fwd1_group_gemm": (P // S, S * Bp, Hp, INp), "fwd2_gemm": (P, Bp, Cp, Hp)}
+    if kernel in forms:
+        groups, rows, n, k = forms[kernel]
+        if n >= 64 and (rows > 32 or 4 * groups * n * k <= (256 if rows > 16 else 64) << 20):
+            return SPLIT3_PEAK_TFLOPS
+    return FP32_MFMA_PEAK_TFLOPS
 
 
 # ---------------------------------------------------------------- one workload
@@ -280,12 +293,14 @@ def summarize(name, c, ms_round, stats, dur_ms):
                     "round_GBps": round(round_bytes / (ms_round * 1e-3) / 1e9, 1)})
         out["round_frac"] = round(out["round_GBps"] / HBM_PEAK_GBS, 4)
         return out
-    fl, by = step_work(c)
+    _, by = step_work(c)
     steps = P * K1 * K2
     out.update({"B": c["B"], "lr": c["lr"], "N": c["N"], "learner_steps_per_round": steps,
                 "learner_steps_per_s": round(steps / (ms_round * 1e-3), 1),
                 "schedule": "delayed" if "fwd1_block_gemm" in stats else "eager",
-                "round_mfma_frac": round(steps * fl / (ms_round * 1e-3) / 1e12 / SPLIT2_PEAK_TFLOPS, 4),
+                # the stated flops of the round's launches, each at the peak of its form, over the round
+                "round_mfma_frac": round(sum(n * work.get(k, (0, 0))[1] / mfma_peak(k, c)
+                                             for k, (n, _) in stats.items()) / 1e12 / (ms_round * 1e-3), 4),
                 "round_alg_bytes_frac": round(steps * by / (ms_round * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)})
     return out
 

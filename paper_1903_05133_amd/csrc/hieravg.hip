@@ -379,8 +379,8 @@ int64_t plan(hieravg* h, int B) {
   }
   h->upd_mean = mlp && h->fused && c.S > 1 && !h->fused_mean && step_w1_mean_supported(h->Bp, c.S);
   h->upd_global = mlp && h->fused && step_w1_mean_supported(h->Bp, P);
-  h->w2_fused = mlp && c.classes > kSmallC && bwd_hidden_update_supported(B, (int)round_up(c.classes, 16)) && c.momentum == 0.0f &&
-                c.weight_decay == 0.0f;
+  h->w2_fused = mlp && c.classes > kSmallC && bwd_hidden_update_supported(B, (int)round_up(c.classes, 16)) &&
+                c.momentum == 0.0f && c.weight_decay == 0.0f;
   h->head_fused = mlp && c.classes <= kSmallC && head_fused_supported((int)h->Hp, (int)round_up(c.classes, 16));
   if (h->upd_mean) {
     plan_split(P / c.S, c.S * h->Bp, (int)n1, (int)h->INp, false, &h->KS_g, &h->cps_g);
@@ -1887,7 +1887,8 @@ int hieravg_evaluate(hieravg_t h, int32_t replica, int32_t split, int64_t n_rows
     h->eval_hit = nullptr;
     h->eval_rows = 0;
     if ((rc = alloc_zero(h, (void**)&h->eval_iota, sizeof(int32_t) * chunk, "evaluation rows")) ||
-        (rc = alloc_zero(h, (void**)&h->eval_part, sizeof(float) * ks1 * chunk * (mlp ? Hp : Cp), "evaluation partials")) ||
+        (rc = alloc_zero(h, (void**)&h->eval_part, sizeof(float) * ks1 * chunk * (mlp ? Hp : Cp),
+                         "evaluation partials")) ||
         (rc = alloc_zero(h, (void**)&h->eval_loss, sizeof(float) * chunk, "evaluation losses")) ||
         (rc = alloc_zero(h, (void**)&h->eval_hit, sizeof(int32_t) * chunk, "evaluation hits")))
       return rc;

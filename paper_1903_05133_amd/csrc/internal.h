@@ -445,7 +445,8 @@ void launch_softmax_grad(hipStream_t s, const float* part, int KS, const float* 
 // over a cluster's samples.
 void launch_bwd_hidden(hipStream_t s, const float* G2, float* W2, int64_t w_pitch, const float* Z1, float* G1, int P,
                        int M, int Mp, int C, int Cp, int Hp, float* b1 = nullptr, const float* lr = nullptr,
-                       float* vb1 = nullptr, float mu = 0.0f, float wd = 0.0f, float* b2 = nullptr, uint32_t* gmax = nullptr, int gS = 1);
+                       float* vb1 = nullptr, float mu = 0.0f, float wd = 0.0f, float* b2 = nullptr, uint32_t* gmax = nullptr,
+                       int gS = 1);
 // Whether launch_bwd_hidden takes the second layer's step for M samples.
 bool bwd_hidden_update_supported(int M, int Cp);
 // Heavy-ball delayed updates, after a block's last step: Gu[k] = u_{K1-1-k}

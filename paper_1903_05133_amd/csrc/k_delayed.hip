@@ -447,7 +447,8 @@ enum FwdTile { FT_256, FT_128x256, FT_128, FT_64, FT_32 };
 struct FwdTileShape {
   int bm, bn, wgs;  // rows, columns, workgroups a launch aims for
 };
-static constexpr FwdTileShape kFwdTiles[] = {{256, 256, 256}, {128, 256, 256}, {128, 128, 256}, {64, 128, 512}, {32, 128, 1024}};
+static constexpr FwdTileShape kFwdTiles[] = {
+    {256, 256, 256}, {128, 256, 256}, {128, 128, 256}, {64, 128, 512}, {32, 128, 1024}};
 static int64_t fwd_tiles(FwdTile t, int64_t groups, int GM, int N) {
   return groups * ((GM + kFwdTiles[t].bm - 1) / kFwdTiles[t].bm) * ((N + kFwdTiles[t].bn - 1) / kFwdTiles[t].bn);
 }
@@ -892,7 +893,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int r = 0; r < 16; ++r) {
       const int m = mt * kGB + wm + 32 * i + 8 * (r >> 2) + 4 * lhi + (r & 3), k = m / Bp;
       if (m < R && n < R && k2 < k)
-        out[((int64_t)(k * K1 + k2) * Bp + (m - k * Bp)) * Bp + s2] = __builtin_amdgcn_ldexpf(acc.sum[i][0][r], -2 * xexp);
+        out[((int64_t)(k * K1 + k2) * Bp + (m - k * Bp)) * Bp + s2] =
+            __builtin_amdgcn_ldexpf(acc.sum[i][0][r], -2 * xexp);
     }
 }
 

@@ -1647,8 +1647,8 @@ void launch_bwd_hidden(hipStream_t s, const float* G2, float* W2, int64_t w_pitc
   const int htiles = Hp / kBhN, mtiles = (M + kBhM - 1) / kBhM;
   const unsigned grid = (unsigned)((int64_t)P * mtiles * htiles);
   if (b2)
-    launch(k_bwd_hidden_mfma<true>, grid, 256, 0, s, G2, W2, w_pitch, Z1, G1, M, Mp, Cp, Hp, htiles, mtiles, b1, lr, vb1,
-           mu, wd, b2, gmax, gS);
+    launch(k_bwd_hidden_mfma<true>, grid, 256, 0, s, G2, W2, w_pitch, Z1, G1, M, Mp, Cp, Hp, htiles, mtiles, b1, lr,
+           vb1, mu, wd, b2, gmax, gS);
   else
     launch(k_bwd_hidden_mfma<false>, grid, 256, 0, s, G2, W2, w_pitch, Z1, G1, M, Mp, Cp, Hp, htiles, mtiles, b1, lr,
            vb1, mu, wd, (float*)nullptr, gmax, gS);
