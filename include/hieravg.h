@@ -128,7 +128,8 @@ typedef struct hieravg_config {
                           momentum = weight_decay = 0 the step is Algorithm 1's
                           plain SGD step.  The paper states no optimizer beyond
                           SGD; these follow the usual heavy-ball convention.
-                          Softmax/MLP with either set run EAGER updates. */
+                          The MLP's schedules with either set: see
+                          HIERAVG_UPDATE_*; softmax runs EAGER updates. */
   int32_t avg_momentum; /* 1: every local and global mean also averages the
                            momentum buffers v; 0: v stays per learner (Algorithm 1
                            averages parameters only) */

@@ -12,6 +12,12 @@
 // where that is more); three products are accumulated, and the one left out
 // is below 2^-22 of the product.
 //
+// The two forms are published: G. Henry, P. Tang and A. Heinecke, "Leveraging
+// the bfloat16 artificial intelligence datatype for higher-precision
+// computations", ARITH 2019 (three bf16 parts); H. Ootomo and R. Yokota,
+// "Recovering single precision accuracy from Tensor Cores while surpassing the
+// FP32 theoretical peak performance", 2022 (two scaled half-precision parts).
+//
 // The rounding of the float32 accumulators dominates the errors.  A product
 // of parts rounds its sum once per 16 terms, a float32 MFMA once per 4 (16x16x4)
 // or 2 (32x32x2).  Where all six products of three parts round one sum, runs
